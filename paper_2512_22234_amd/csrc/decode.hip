@@ -2,30 +2,41 @@
 // of DiRL Section 2.1 used in rollouts.  While block k is denoised, its S noisy
 // queries attend to the clean tokens of the blocks before it (the cache) and
 // to each other in both directions (Eq. 2); nothing else exists yet, so there
-// is no mask beyond the lengths.  Every cached K/V row is read once per
-// (sequence, KV head, query tile) and serves up to 32 query rows of that KV
-// head: the work is bound by HBM bandwidth, not by the MFMAs.
+// is no mask beyond the lengths.  Every cached K/V row is read once per item
+// and serves all of the item's query rows: the work is bound by HBM bandwidth,
+// not by the MFMAs.
 //
-// Work items are (sequence b, KV head, 32-row tile of the G*S query rows);
-// an item's keys are its cache_lens[b] cached rows followed by the block's S
-// rows, cut into 32-key tiles (cache tiles, then block tiles; none straddles
-// the two arrays).  Lay the tiles of all items end to end, in item order: T
-// tiles in all.  Wave gw of the DEC_WAVES waves takes the contiguous run
-// [gw*T/DEC_WAVES, (gw+1)*T/DEC_WAVES), whatever the lengths, so every wave
-// streams the same number of bytes and a long cache is spread over many waves
-// while short ones share a wave.  The lengths live on the device: every
-// workgroup scans them once to find where its waves start.
+// Work items are (sequence b, KV head, group of the G*S query rows); an item's
+// keys are its cache_lens[b] cached rows followed by the block's S rows, cut
+// into KT-key tiles (cache tiles, then block tiles; none straddles the two
+// arrays).  A team of TW waves, one per 32 query rows, works on an item.  Lay
+// the tiles of all items end to end, in item order: T tiles in all.  Team gw of
+// the n teams that take part takes the contiguous run [gw*T/n, (gw+1)*T/n),
+// whatever the lengths, so every team streams the same number of bytes and a
+// long cache is spread over many teams while short ones share one.  The
+// lengths live on the device: every workgroup scans them once to find where
+// its teams start.  Short calls use fewer teams (dec_runs).
 //
 // A wave keeps an online-softmax state for the item it is in and flushes it
 // when the item or the run ends: an item that lies wholly inside one run is
 // written out (O, LSE) at once; otherwise each run leaves its unnormalised O,
 // max and sum in a partial slot, and dec_combine_kernel merges the runs of the
-// item.  Slot gw + item is unique: two runs (gw, item) and (gw', item') with
-// gw < gw' and item > item' cannot both hold tiles, since both the runs and
-// the items are contiguous and in the same order.
+// item.  The slot of (gw, item) starts at row gw * rows-per-group + (first row
+// of the item's group, all items' rows laid end to end), so slots never
+// overlap: two runs (gw, item) and (gw', item') with gw < gw' and item > item'
+// cannot both hold tiles, since both the runs and the items are contiguous and
+// in the same order.
 //
-// The waves never wait for each other: each double-buffers its own LDS tiles
-// (copies go straight from HBM to LDS) and waits only for its own copies.
+// Teams never wait for each other.  Tiles go straight from HBM to an LDS ring
+// of NST stages per team, NST - 1 tiles ahead.
+//   TW = 1 (up to 32 query rows per KV head): four teams per workgroup, each
+//     wave waits only for its own copies.
+//   TW = 2, 4 (up to 64 rows, more): a workgroup is one team, whose waves share
+//     each tile, so a KV row is fetched once for up to 128 query rows; one
+//     barrier per tile.  24 sequences of 512..8192 tokens, 32 query and 8 KV
+//     heads of 128, S = 32 (128 rows per KV head): 93 us, 4.0 TB/s; with one
+//     wave per 32 rows, which fetched the cache four times, 203 us.  (Tiles of
+//     32 keys: 104 us; eight waves, half the keys of a tile each: 95 us.)
 // Per tile: S^T = K Q^T (a lane owns a query column, as in the forward pass),
 // P = exp2(c S - m) against a lazily moved reference max, O^T += V^T P^T with
 // V^T read through the transposing LDS read.
@@ -45,9 +56,13 @@ struct DecParams {
   bf16* O;                // [B][Hq][S][D]
   float* LSE;             // [B][Hq][S]
   int4* desc;             // [item]: first run, last run (-1: the item was written directly), T
-  float* part;            // [slot][32 rows][D + 4]: unnormalised O, max (log2 units), sum
-  int B, S, Hq, Hkv, G, C, nqt;
-  float c;  // scale * log2(e)
+  float* part;            // [row][D + 4]: unnormalised O, max (log2 units), sum
+  int B, S, Hq, Hkv, G, C;
+  int ng;     // row groups per (sequence, KV head)
+  int grows;  // query rows of a group (a multiple of 32, at most 32 * TW)
+  int hrows;  // partial rows of a (sequence, KV head): its G*S rows rounded up to 32
+  int runs;   // teams of the grid
+  float c;    // scale * log2(e)
 };
 
 // Cache length of sequence b, clamped to [0, C].  `lens` is p.cache_lens
@@ -57,22 +72,37 @@ __device__ inline int dec_len(const DecParams& p, const int* __restrict__ lens, 
   return imin(imax(lens[b], 0), p.C);
 }
 // Key tiles of an item of a sequence with cache length len.
-__device__ inline int dec_tiles(const DecParams& p, int len) { return cdiv(len, DEC_KT) + cdiv(p.S, DEC_KT); }
-// First tile of run gw (the runs cut T tiles into DEC_WAVES near-equal pieces).
-__device__ inline int dec_run_start(int gw, int T) { return (int)(((long long)gw * T) / DEC_WAVES); }
+template <int KT>
+__device__ inline int dec_tiles(const DecParams& p, int len) {
+  return cdiv(len, KT) + cdiv(p.S, KT);
+}
+// Teams that take part in a call of T tiles on a grid of `runs` teams: at
+// least about DEC_MIN_RUN tiles each, so that a short call is not cut into
+// single tiles with as many partial results to merge (1, 2 and 4 measured the
+// same within 2% on one sequence of 1500 tokens), and no run is empty (T >= 1).
+constexpr int DEC_MIN_RUN = 2;
+__device__ inline int dec_runs(int runs, int T) { return imin(runs, cdiv(T, DEC_MIN_RUN)); }
+// First tile of run gw (the runs cut T tiles into n near-equal pieces).
+__device__ inline int dec_run_start(int gw, int n, int T) { return (int)(((long long)gw * T) / n); }
+// First row of the partial slot of run gw for row group g of (sequence, KV head) bh.
+__device__ inline size_t dec_slot_row(const DecParams& p, int gw, size_t bh, int g) {
+  return (size_t)(gw + g) * p.grows + bh * p.hrows;
+}
 
 // Position of a tile: sequence b (cache length len, nt tiles per item), item
-// r of the sequence (KV head r / nqt, query tile r % nqt), tile j of the item.
+// r of the sequence (KV head r / ng, row group r % ng), tile j of the item.
 struct DecPos {
   int b, len, nt, r, j;
 };
 
-template <int D>
+template <int D, int TW, int KT, int NST>
 struct DecSmem {
-  static constexpr uint32_t TILE = DEC_KT * D * 2;  // bytes of one swizzled 32-key tile
-  alignas(256) char buf[4][4 * TILE];                // per wave: K and V, double-buffered
-  int wsum[4];                                       // prologue: per-wave sums of the scan
-  int start_b[4], start_off[4];                      // where each wave's run starts
+  static constexpr int TEAMS = TW == 1 ? 4 : 1;      // teams per workgroup
+  static constexpr int NW = TW * TEAMS;              // waves per workgroup
+  static constexpr uint32_t TILE = KT * D * 2;       // bytes of one swizzled K or V tile
+  alignas(256) char buf[TEAMS][NST * 2 * TILE];      // per team: a ring of K and V tiles
+  int wsum[NW];                                      // prologue: per-wave sums of the scan
+  int start_b[TEAMS], start_off[TEAMS];              // where each team's run starts
 };
 
 // The reference maximum of a row moves only when the row's scores exceed it
@@ -80,24 +110,26 @@ struct DecSmem {
 // float32 sums, and most tiles skip the rescale.
 constexpr float DEC_SLACK = 8.0f;
 
-template <int D>
-__global__ __launch_bounds__(256, 1) void dec_kernel(DecParams p, const int* __restrict__ lens) {
-  constexpr int DS = D / 16, DB = D / 32, PST = D + 4;
-  using Smem = DecSmem<D>;
+template <int D, int TW, int KT, int NST>
+__global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecParams p, const int* __restrict__ lens) {
+  constexpr int DS = D / 16, DB = D / 32, PST = D + 4, KB = KT / 32;
+  using Smem = DecSmem<D, TW, KT, NST>;
+  constexpr int TEAMS = Smem::TEAMS, NW = Smem::NW, NT = 64 * NW;
   __shared__ Smem sm;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g2 = lane >> 5;
-  const int I = p.Hkv * p.nqt;  // items per sequence
+  const int tm = TW == 1 ? w : 0, tw = TW == 1 ? 0 : w;  // team of the workgroup, wave of the team
+  const int I = p.Hkv * p.ng;                            // items per sequence
 
-  // ---- prologue: T, and the position of each wave's first tile ----
+  // ---- prologue: T, and the position of each team's first tile ----
   // thread t sums the tiles per item of sequences [t*cpt, (t+1)*cpt)
-  const int cpt = cdiv(p.B, 256);
+  const int cpt = cdiv(p.B, NT);
   const int c0 = imin(p.B, tid * cpt), c1 = imin(p.B, c0 + cpt);
   int csum = 0;
 #pragma unroll 4
-  for (int b = c0; b < c1; ++b) csum += dec_tiles(p, dec_len(p, lens, b));
+  for (int b = c0; b < c1; ++b) csum += dec_tiles<KT>(p, dec_len(p, lens, b));
   int incl = csum;  // inclusive scan over the wave
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -108,21 +140,24 @@ __global__ __launch_bounds__(256, 1) void dec_kernel(DecParams p, const int* __r
   __syncthreads();
   int before = 0, total = 0;
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
+  for (int v = 0; v < NW; ++v) {
     const int s = sm.wsum[v];
     before += v < w ? s : 0;
     total += s;
   }
   const int excl = before + incl - csum;  // tiles per item of the sequences before c0
   const int T = total * I;                // checked on the host to fit in 31 bits
-  // the thread whose sequences hold a wave's first tile records where it lies
+  const int n = dec_runs(p.runs, T);
+  // Consecutive runs go to different workgroups: where fewer teams than the
+  // grid holds take part, they are spread over the CUs.
+  // the thread whose sequences hold a team's first tile records where it lies
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int x0 = dec_run_start(blockIdx.x * 4 + v, T);
+  for (int v = 0; v < TEAMS; ++v) {
+    const int x0 = dec_run_start(v * gridDim.x + blockIdx.x, n, T);
     if (csum > 0 && excl * I <= x0 && x0 < (excl + csum) * I) {
       int pb = excl;
       for (int b = c0; b < c1; ++b) {
-        const int nt = dec_tiles(p, dec_len(p, lens, b));
+        const int nt = dec_tiles<KT>(p, dec_len(p, lens, b));
         if (x0 < (pb + nt) * I) {
           sm.start_b[v] = b;
           sm.start_off[v] = x0 - pb * I;
@@ -134,15 +169,15 @@ __global__ __launch_bounds__(256, 1) void dec_kernel(DecParams p, const int* __r
   }
   __syncthreads();
 
-  // ---- this wave's run ----
-  const int gw = blockIdx.x * 4 + w;
-  const int x0 = dec_run_start(gw, T), x1 = dec_run_start(gw + 1, T);
-  if (x0 >= x1) return;
+  // ---- this team's run ----
+  const int gw = tm * gridDim.x + blockIdx.x;
+  if (gw >= n) return;
+  const int x0 = dec_run_start(gw, n, T), x1 = dec_run_start(gw + 1, n, T);
   DecPos pc;
-  pc.b = __builtin_amdgcn_readfirstlane(sm.start_b[w]);
-  const int off = __builtin_amdgcn_readfirstlane(sm.start_off[w]);
+  pc.b = __builtin_amdgcn_readfirstlane(sm.start_b[tm]);
+  const int off = __builtin_amdgcn_readfirstlane(sm.start_off[tm]);
   pc.len = __builtin_amdgcn_readfirstlane(dec_len(p, lens, pc.b));
-  pc.nt = dec_tiles(p, pc.len);
+  pc.nt = dec_tiles<KT>(p, pc.len);
   pc.r = off / pc.nt;
   pc.j = off - pc.r * pc.nt;
   const int S = p.S;
@@ -154,20 +189,20 @@ __global__ __launch_bounds__(256, 1) void dec_kernel(DecParams p, const int* __r
         q.r = 0;
         if (++q.b < p.B) {
           q.len = __builtin_amdgcn_readfirstlane(dec_len(p, lens, q.b));
-          q.nt = dec_tiles(p, q.len);
+          q.nt = dec_tiles<KT>(p, q.len);
         }
       }
     }
     return q;
   };
-  // this lane's query row of item (b, r): row qt*32 + l32 of the G*S rows of
-  // KV head r / nqt (those rows are consecutive in Q, O and LSE).  A lane
-  // past the last row takes the last row instead: its score column is
+  // this lane's query row of item (b, r): row g*grows + 32*tw + l32 of the G*S
+  // rows of KV head r / ng (those rows are consecutive in Q, O and LSE).  A
+  // lane past the last row takes the last row instead: its score column is
   // computed like the others (columns never mix) and never stored.
   auto query_row = [&](DecPos q, bool& valid) {
-    const int hkv = q.r / p.nqt, R = (q.r - hkv * p.nqt) * DEC_QT + l32;
-    valid = R < p.G * S;
-    return ((size_t)q.b * p.Hq + (size_t)hkv * p.G) * S + (valid ? R : p.G * S - 1);
+    const int hkv = q.r / p.ng, g = q.r - hkv * p.ng, rl = 32 * tw + l32, R = g * p.grows + rl;
+    valid = R < p.G * S && (TW == 1 || rl < p.grows);
+    return ((size_t)q.b * p.Hq + (size_t)hkv * p.G) * S + (R < p.G * S ? R : p.G * S - 1);
   };
   struct QRows {
     bf16x8 v[DS];
@@ -181,14 +216,14 @@ __global__ __launch_bounds__(256, 1) void dec_kernel(DecParams p, const int* __r
     return r;
   };
 
-  const TileCopy<D, DEC_KT, 64> copy(lane);  // one wave copies a whole tile
+  const TileCopy<D, KT, 64 * TW> copy(TW == 1 ? lane : tid);  // the team copies a whole tile
   constexpr int NI = decltype(copy)::NI;
   // copy K and V of the tile at q to dst, dst + TILE
   auto issue = [&](DecPos q, char* dst) {
-    const size_t grp = (size_t)q.b * p.Hkv + q.r / p.nqt;
-    const int ntc = cdiv(q.len, DEC_KT);
+    const size_t grp = (size_t)q.b * p.Hkv + q.r / p.ng;
+    const int ntc = cdiv(q.len, KT);
     const bool cached = q.j < ntc;
-    const int r0 = (cached ? q.j : q.j - ntc) * DEC_KT;
+    const int r0 = (cached ? q.j : q.j - ntc) * KT;
     const int left = (cached ? q.len : S) - r0;
     const size_t off2 = (cached ? grp * p.C : grp * S) * D + (size_t)r0 * D;
     copy.issue_rows((cached ? p.Kc : p.Kn) + off2, left, dst);
@@ -208,9 +243,20 @@ __global__ __launch_bounds__(256, 1) void dec_kernel(DecParams p, const int* __r
     lsum = 0.f;
   };
   reset();
-  char* const mine = sm.buf[w];
-  qreg = load_q(pc);
-  issue(pc, mine);
+  char* const ring = sm.buf[tm];
+  if (TW == 1) qreg = load_q(pc);
+  // the first NST - 1 tiles (those this run has); pa: the next tile to copy
+  DecPos pa = pc;
+#pragma unroll
+  for (int u = 0; u < NST - 1; ++u)
+    if (x0 + u < x1) {
+      issue(pa, ring + u * 2 * Smem::TILE);
+      pa = advance(pa);
+    }
+  if (TW > 1) {
+    qreg = load_q(pc);
+    wait_global_loads();
+  }
   int item_start = x0 - pc.j;  // flat index of the current item's first tile
   int seg_j0 = pc.j;           // tile of the item this run's segment starts at
 
@@ -234,11 +280,12 @@ __global__ __launch_bounds__(256, 1) void dec_kernel(DecParams p, const int* __r
         }
         if (g2 == 0) p.LSE[qrow] = (m + __log2f(Lrow)) * LN2;
       }
-      if (lane == 0) p.desc[item] = int4{0, -1, T, 0};
+      if (lane == 0 && tw == 0) p.desc[item] = int4{0, -1, T, 0};
       return;
     }
     if (valid) {
-      float* pr = p.part + ((size_t)(gw + item) * DEC_QT + l32) * PST;
+      const int hkv = pc.r / p.ng;
+      float* pr = p.part + (dec_slot_row(p, gw, (size_t)pc.b * p.Hkv + hkv, pc.r - hkv * p.ng) + 32 * tw + l32) * PST;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -248,54 +295,78 @@ __global__ __launch_bounds__(256, 1) void dec_kernel(DecParams p, const int* __r
         }
       if (g2 == 0) *reinterpret_cast<f32x4*>(pr + D) = f32x4{m, Lrow, 0.f, 0.f};
     }
-    if (ends && lane == 0) {
+    if (ends && lane == 0 && tw == 0) {
       // the runs holding this item: from the one holding its first tile to this one
-      const int first = (int)((((long long)item_start + 1) * DEC_WAVES - 1) / T);
+      const int first = (int)((((long long)item_start + 1) * n - 1) / T);
       p.desc[item] = int4{first, gw, T, 0};
     }
   };
 
-  // One tile: `cur` holds the tile at pc; the copy of the next tile (at pn,
-  // if this run has one) goes to `nxt`.  The restrict qualifiers tell the
-  // compiler that the copy in flight does not touch `cur`, so its reads need
-  // not wait for it.  Query rows of the next item are loaded a tile ahead,
-  // after the wait for the current tile (which covers the current item's
-  // query rows, loaded before the next tile's copy): copies and query loads
-  // complete in issue order.
-  auto step = [&](const char* __restrict__ cur, char* __restrict__ nxt, DecPos pn, bool more,
+  // One tile: `cur` holds the tile at pc; the copy of the tile NST - 1 ahead
+  // (at pa, if this run has one) goes to `nxt`, whose last readers are done.
+  // The restrict qualifiers tell the compiler that the copy in flight does not
+  // touch `cur`, so its reads need not wait for it.
+  auto step = [&](const char* __restrict__ cur, char* __restrict__ nxt, DecPos pn, bool copies,
                   bool new_item) __attribute__((always_inline)) {
     compute_fence();  // the reads of the buffer about to be refilled are done
-    // (the query-row copy sits in both branches so that the compiler's own
-    // wait for it counts the copy just issued on the first one)
-    if (more) {
-      issue(pn, nxt);
-      wait_global_loads_but<2 * NI>();  // the tile at pc has landed (this wave's own copy)
-      if (new_item) qreg = qnext;
-      if (pn.j == 0) qnext = load_q(pn);
+    if constexpr (TW == 1) {
+      // Query rows of the next item (the tile at pn) are loaded a tile ahead,
+      // after the wait for the current tile: copies and query loads complete in
+      // issue order.  (The query-row copy sits in both branches so that the
+      // compiler's own wait for it counts the copy just issued on the first one.)
+      if (copies) {
+        issue(pa, nxt);
+        wait_global_loads_but<(NST - 1) * 2 * NI>();  // the tile at pc has landed (this wave's own copy)
+        if (new_item) qreg = qnext;
+        if (pn.j == 0) qnext = load_q(pn);
+      } else {
+        wait_global_loads();
+        if (new_item) qreg = qnext;
+      }
     } else {
-      wait_global_loads();
-      if (new_item) qreg = qnext;
+      if (copies) wait_global_loads_but<(NST - 2) * 2 * NI>();  // this wave's part of the tile at pc has landed
+      else wait_global_loads();
+      barrier_lds_only();  // ... every wave's; and all are done with `nxt`
+      if (copies) issue(pa, nxt);
+      // A new item's query rows, waited for at once: were they still in flight
+      // at the end of this branch, the compiler would wait for them, and so for
+      // every copy in flight, in front of each tile's first product (121 instead
+      // of 95 us for the call above).
+      if (new_item) {
+        qreg = load_q(pc);
+        wait_global_loads();
+      }
     }
-    const int ntc = cdiv(pc.len, DEC_KT);
-    const int nvalid = pc.j < ntc ? pc.len - pc.j * DEC_KT : S - (pc.j - ntc) * DEC_KT;  // keys that exist
+    const int ntc = cdiv(pc.len, KT);
+    const int nvalid = pc.j < ntc ? pc.len - pc.j * KT : S - (pc.j - ntc) * KT;  // keys that exist
 
     // S^T[key][query] = sum_d K[key][d] Q[query][d]
-    f32x16 sacc;
+    f32x16 sacc[KB];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) sacc[e] = 0.f;
+    for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-    for (int s = 0; s < DS; ++s) sacc = mfma32(lds_rows<D>(cur, ops.row_rel, s, 0), qreg.v[s], sacc);
-    if (nvalid < DEC_KT) {
+      for (int e = 0; e < 16; ++e) sacc[kb][e] = 0.f;
 #pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4)
+    for (int s = 0; s < DS; ++s)
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
-          if (8 * i4 + 4 * g2 + jj >= nvalid) sacc[4 * i4 + jj] = -INFINITY;
+      for (int kb = 0; kb < KB; ++kb) sacc[kb] = mfma32(lds_rows<D>(cur, ops.row_rel, s, kb), qreg.v[s], sacc[kb]);
+    pipeline_lds_reads<DS * KB, 4, 1>();  // operand reads four MFMAs ahead
+    if (nvalid < KT) {
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4)
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj)
+            if (32 * kb + 8 * i4 + 4 * g2 + jj >= nvalid) sacc[kb][4 * i4 + jj] = -INFINITY;
     }
-    float mx = -INFINITY;
+    // (row maximum and row sum as balanced trees: no serial chains)
+    float m3[KB * 8];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[e]);
-    mx = halves_max(mx) * p.c;
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int e = 0; e < 16; e += 2) m3[kb * 8 + e / 2] = fmaxf(sacc[kb][e], sacc[kb][e + 1]);
+    const float mx = halves_max(tree_max<KB * 8>(m3)) * p.c;
     const bool grow = mx > m + DEC_SLACK;
     if (__any(grow)) {
       const float alpha = grow ? fast_exp2(m - mx) : 1.f;
@@ -306,25 +377,33 @@ __global__ __launch_bounds__(256, 1) void dec_kernel(DecParams p, const int* __r
 #pragma unroll
         for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
     }
+    bf16x8 pb[2 * KB];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const float x = fast_exp2(sacc[e] * p.c - m);
-      sacc[e] = x;
-      lsum += x;
+    for (int kb = 0; kb < KB; ++kb) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sacc[kb][e] = fast_exp2(sacc[kb][e] * p.c - m);
+      pb[2 * kb] = pack8(sacc[kb], 0);
+      pb[2 * kb + 1] = pack8(sacc[kb], 8);
     }
-    const bf16x8 pb[2] = {pack8(sacc, 0), pack8(sacc, 8)};
+    lsum += tree_sum<KB>(sacc);
     // O^T[d][query] += sum_key V^T[d][key] P^T[key][query]
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < 2 * KB; ++c)
 #pragma unroll
       for (int db = 0; db < DB; ++db)
         oacc[db] = mfma32(lds_tr<D>(cur + Smem::TILE, ops.tr_rel0, ops.tr_rel1, c, db), pb[c], oacc[db]);
+    pipeline_lds_reads<2 * KB * DB, 4, 2>();
   };
 
-  for (int x = x0, i = 0; x < x1; ++x, ++i) {
+  uint32_t bcur = 0;                           // ring offset of the tile at pc
+  uint32_t bnxt = (NST - 1) * 2 * Smem::TILE;  // ring offset the copy NST - 1 ahead goes to
+  for (int x = x0; x < x1; ++x) {
     const DecPos pn = advance(pc);
-    const bool more = x + 1 < x1;
-    step(mine + (i & 1) * 2 * Smem::TILE, mine + ((i + 1) & 1) * 2 * Smem::TILE, pn, more, x > x0 && pc.j == 0);
+    const bool more = x + 1 < x1, copies = x + NST - 1 < x1;
+    step(ring + bcur, ring + bnxt, pn, copies, x > x0 && pc.j == 0);
+    if (copies) pa = advance(pa);
+    bnxt = bcur;
+    bcur = bcur == (NST - 1) * 2 * Smem::TILE ? 0u : bcur + 2 * Smem::TILE;
     if (!more || pn.j == 0) {
       flush();
       if (more) {  // the next tile starts the next item
@@ -337,44 +416,76 @@ __global__ __launch_bounds__(256, 1) void dec_kernel(DecParams p, const int* __r
   }
 }
 
-// Merge the runs of each query row of an item held by several waves:
+// Merge the runs of each query row of an item held by several teams:
 // O = sum_r 2^(m_r - M) O_r / sum_r 2^(m_r - M) l_r with M = max_r m_r, over
-// the runs of waves first..last that hold tiles, merged in one pass (the
-// running maximum moves as runs are added, so every run's loads are
-// independent of the others' results).  One thread per (query row, 4
-// features); rows are those of Q, so no thread is spent on padding rows of a
-// query tile.
-template <int D>
+// the runs first..last, merged in one pass (the running maximum moves as runs
+// are added, so every run's loads are independent of the others' results).
+// One thread per (query row, 4 features, part of the runs): P threads take
+// every P-th run each and meet in LDS, in part order.  Rows are those of Q, so
+// no thread is spent on padding rows.  Bound by the latency of its dependent
+// loads: where few items share the teams (eight runs or more each), P = 8
+// (one sequence of 1500 tokens, 24 runs per item: 4 us, against 32 us for one
+// thread over the 128 runs it had with empty ones); with more items one
+// thread takes the few runs of each (64 sequences: 6.2 us either way).
+template <int D, int P>
 __global__ __launch_bounds__(256) void dec_combine_kernel(DecParams p) {
-  constexpr int TPR = D / 4, PST = D + 4;
-  const size_t gid = (size_t)blockIdx.x * 256 + threadIdx.x;
-  const size_t qrow = gid / TPR;  // row of Q: ((b * Hq + h) * S + s)
-  const int q4 = (int)(gid % TPR);
+  constexpr int TPR = D / 4, PST = D + 4, RPW = 256 / (TPR * P);  // rows per workgroup
+  static_assert(RPW >= 1, "a workgroup holds whole rows");
+  __shared__ f32x4 so[P > 1 ? 256 : 1];
+  __shared__ float2 sml[P > 1 ? 256 : 1];
+  const int tid = threadIdx.x;
+  const int q4 = tid % TPR, part = (tid / TPR) % P;
+  const size_t qrow = (size_t)blockIdx.x * RPW + tid / (TPR * P);  // row of Q: ((b * Hq + h) * S + s)
   const int GS = p.G * p.S;
-  if (qrow >= (size_t)p.B * p.Hkv * GS) return;
-  const int R = (int)(qrow % GS);
-  const size_t bh = qrow / GS;  // b * Hkv + hkv
-  const int item = (int)(bh * p.nqt) + R / DEC_QT, r = R % DEC_QT;
-  const int4 d = p.desc[item];
-  if (d.y < 0) return;  // written by the decode kernel itself
-  const int T = d.z;
+  int4 d = {0, -1, 0, 0};
   float M = -INFINITY, Lr = 0.f;
   f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  if (qrow < (size_t)p.B * p.Hkv * GS) {
+    const int R = (int)(qrow % GS);
+    const size_t bh = qrow / GS;  // b * Hkv + hkv
+    const int g = R / p.grows, r = R - g * p.grows;
+    d = p.desc[bh * p.ng + g];  // (last run -1: written by the decode kernel itself)
 #pragma unroll 4
-  for (int gw = d.x; gw <= d.y; ++gw) {
-    const float* ps = p.part + ((size_t)(gw + item) * DEC_QT + r) * PST;
-    const f32x4 ml = *reinterpret_cast<const f32x4*>(ps + D);
-    const f32x4 v = *reinterpret_cast<const f32x4*>(ps + 4 * q4);
-    if (dec_run_start(gw, T) == dec_run_start(gw + 1, T)) continue;  // a wave without tiles wrote nothing
-    const float Mn = fmaxf(M, ml[0]);
-    const float a = fast_exp2(M - Mn), c = fast_exp2(ml[0] - Mn);  // a = 0 for the first run (M = -inf)
-    Lr = Lr * a + ml[1] * c;
-    o = o * a + v * c;
-    M = Mn;
+    for (int gw = d.x + part; gw <= d.y; gw += P) {
+      const float* ps = p.part + (dec_slot_row(p, gw, bh, g) + r) * PST;
+      const f32x4 ml = *reinterpret_cast<const f32x4*>(ps + D);
+      const f32x4 v = *reinterpret_cast<const f32x4*>(ps + 4 * q4);
+      const float Mn = fmaxf(M, ml[0]);
+      const float a = fast_exp2(M - Mn), c = fast_exp2(ml[0] - Mn);  // a = 0 for the first run (M = -inf)
+      Lr = Lr * a + ml[1] * c;
+      o = o * a + v * c;
+      M = Mn;
+    }
+  }
+  if constexpr (P > 1) {
+    so[tid] = o;
+    sml[tid] = float2{M, Lr};
+    __syncthreads();
+    if (part != 0 || d.y < 0) return;
+    // (part 0 holds at least one run, so M is finite)
+#pragma unroll
+    for (int u = 1; u < P; ++u) {
+      const float2 ml = sml[tid + u * TPR];
+      const f32x4 v = so[tid + u * TPR];
+      const float Mn = fmaxf(M, ml.x);
+      const float a = fast_exp2(M - Mn), c = fast_exp2(ml.x - Mn);  // c = 0 for a part without runs
+      Lr = Lr * a + ml.y * c;
+      o = o * a + v * c;
+      M = Mn;
+    }
+  } else if (d.y < 0) {
+    return;
   }
   const float inv = 1.f / Lr;
   st_bf16x4(p.O + qrow * D + 4 * q4, o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
   if (q4 == 0) p.LSE[qrow] = (M + __log2f(Lr)) * LN2;
+}
+
+template <int D, int TW, int KT, int NST>
+void launch_dec_kernel(const DecParams& p, hipStream_t st) {
+  using Smem = DecSmem<D, TW, KT, NST>;
+  hipLaunchKernelGGL((dec_kernel<D, TW, KT, NST>), dim3(p.runs / Smem::TEAMS), dim3(64 * Smem::NW), 0, st, p,
+                     p.cache_lens);
 }
 
 template <int D>
@@ -397,13 +508,26 @@ hipError_t launch_decode_d(const DecodeShape& s, const void* Q, const void* Kc, 
   p.Hkv = s.Hkv;
   p.G = s.Hq / s.Hkv;
   p.C = s.C;
-  p.nqt = decode_query_tiles(s);
   p.c = s.scale * LOG2E;
-  hipLaunchKernelGGL(dec_kernel<D>, dim3(DEC_WAVES / 4), dim3(256), 0, st, p, cache_lens);
+  // Row groups: a team of 1, 2 or 4 waves (32 rows each) per group.
+  const DecodeGroups g = decode_groups(s);
+  p.ng = g.ng;
+  p.grows = g.rows;
+  p.hrows = DEC_QT * decode_query_tiles(s);
+  p.runs = g.runs;
+  if (g.waves == 1) launch_dec_kernel<D, 1, 32, 2>(p, st);
+  else if (g.waves == 2) launch_dec_kernel<D, 2, 32, 512 / D>(p, st);
+  else launch_dec_kernel<D, 4, 64, 512 / D>(p, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const size_t threads = (size_t)s.B * s.Hq * s.S * (D / 4);
-  hipLaunchKernelGGL(dec_combine_kernel<D>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, p);
+  const size_t rows = (size_t)s.B * s.Hq * s.S, items = (size_t)s.B * s.Hkv * g.ng;
+  if (items * 8 <= (size_t)g.runs) {
+    constexpr int P = 8, RPW = 256 / (D / 4 * P);
+    hipLaunchKernelGGL((dec_combine_kernel<D, P>), dim3((unsigned)((rows + RPW - 1) / RPW)), dim3(256), 0, st, p);
+  } else {
+    constexpr int RPW = 256 / (D / 4);
+    hipLaunchKernelGGL((dec_combine_kernel<D, 1>), dim3((unsigned)((rows + RPW - 1) / RPW)), dim3(256), 0, st, p);
+  }
   return hipGetLastError();
 }
 

@@ -333,6 +333,32 @@ __device__ inline float halves_sum(float x) {
   return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
 }
 
+// Maximum of N values as a balanced tree (depth log2 N instead of a chain of N).
+template <int N>
+__device__ inline float tree_max(const float* v) {
+  if constexpr (N == 1) {
+    return v[0];
+  } else {
+    return fmaxf(tree_max<N / 2>(v), tree_max<N - N / 2>(v + N / 2));
+  }
+}
+// Sum of the 16 K entries of K accumulators as a balanced tree.
+template <int K>
+__device__ inline float tree_sum(const f32x16* a) {
+  float t[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    t[e] = a[0][e];
+#pragma unroll
+    for (int k = 1; k < K; ++k) t[e] += a[k][e];
+  }
+#pragma unroll
+  for (int w = 8; w > 0; w >>= 1)
+#pragma unroll
+    for (int e = 0; e < w; ++e) t[e] += t[e + w];
+  return t[0];
+}
+
 // Workgroup -> head mapping that keeps all query heads of one KV group on the
 // same XCD (workgroups are dispatched round-robin over the 8 XCDs), so K/V of a
 // group are shared through that XCD's L2.  pos in [0, nbh); falls back to the

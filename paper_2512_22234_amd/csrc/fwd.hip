@@ -48,32 +48,6 @@ struct FwdSmem {
 // reference).
 constexpr float RESCALE_SLACK = 8.0f;
 
-// Maximum of N values as a balanced tree (depth log2 N instead of a chain of N).
-template <int N>
-__device__ inline float tree_max(const float* v) {
-  if constexpr (N == 1) {
-    return v[0];
-  } else {
-    return fmaxf(tree_max<N / 2>(v), tree_max<N - N / 2>(v + N / 2));
-  }
-}
-// Sum of the 16 K entries of K accumulators as a balanced tree.
-template <int K>
-__device__ inline float tree_sum(const f32x16* a) {
-  float t[16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    t[e] = a[0][e];
-#pragma unroll
-    for (int k = 1; k < K; ++k) t[e] += a[k][e];
-  }
-#pragma unroll
-  for (int w = 8; w > 0; w >>= 1)
-#pragma unroll
-    for (int e = 0; e < w; ++e) t[e] += t[e + w];
-  return t[0];
-}
-
 template <int D>
 __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
   constexpr int BM = FWD_BM, BN = FWD_BN;

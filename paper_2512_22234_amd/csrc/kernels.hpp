@@ -192,11 +192,12 @@ inline size_t dkdv_pair_ints(int B, int Hkv, int L) {
 // (capacity C) and the block's own S keys.
 //   Q, O   : [B][Hq][S][D]      K/V cache : [B][Hkv][C][D]
 //   K/V new: [B][Hkv][S][D]     LSE       : [B][Hq][S] float32
-// An item is (sequence, KV head, DEC_QT-row tile of the G*S query rows); its
-// keys (cache, then block) are cut into DEC_KT-key tiles.  The tiles of all
-// items, in item order, are shared out in equal contiguous runs over
-// DEC_WAVES waves (DEC_WAVES / 4 workgroups of four).
+// An item is (sequence, KV head, group of the G*S query rows); its keys (cache,
+// then block) are cut into tiles of DEC_KT (or more) keys.  The tiles of all
+// items, in item order, are shared out in equal contiguous runs over teams of
+// waves, one wave per DEC_QT query rows of a group (DecodeGroups).
 constexpr int DEC_QT = 32, DEC_KT = 32, DEC_WAVES = 1024;
+
 
 struct DecodeShape {
   int B, S, Hq, Hkv, D;
@@ -206,10 +207,26 @@ struct DecodeShape {
 
 inline int decode_query_tiles(const DecodeShape& s) { return (s.Hq / s.Hkv * s.S + DEC_QT - 1) / DEC_QT; }
 inline size_t decode_items(const DecodeShape& s) { return (size_t)s.B * s.Hkv * decode_query_tiles(s); }
+// Row groups of a KV head's G*S query rows and the teams that work on them.
+// Up to 32 rows: one wave.  More: a team of 2 (up to 64 rows) or 4 waves
+// sharing each K/V tile, in as few groups as 128 rows allow, of equal size.
+// Every team's partial rows fit the workspace: runs * rows <= DEC_WAVES * 32.
+struct DecodeGroups {
+  int waves, ng, rows, runs;
+};
+inline DecodeGroups decode_groups(const DecodeShape& s) {
+  const int t = decode_query_tiles(s);
+  DecodeGroups g;
+  g.waves = t == 1 ? 1 : t == 2 ? 2 : 4;
+  g.ng = (t + g.waves - 1) / g.waves;
+  g.rows = DEC_QT * ((t + g.ng - 1) / g.ng);
+  g.runs = DEC_WAVES / g.waves;
+  return g;
+}
 // float32 elements of one partial row: D values, then max and sum (padded to 16 bytes).
 inline int decode_part_stride(int D) { return D + 4; }
 // Workspace: per item a 16-byte descriptor, then the partial results of every
-// (wave, item) run: at most DEC_WAVES + items of them, DEC_QT rows each.
+// (team, item) run: the rows of one group per team, and those of all items.
 inline size_t decode_desc_bytes(const DecodeShape& s) { return (decode_items(s) * 16 + 255) & ~(size_t)255; }
 inline size_t decode_workspace_bytes(const DecodeShape& s) {
   return decode_desc_bytes(s) + (DEC_WAVES + decode_items(s)) * DEC_QT * decode_part_stride(s.D) * 4;

@@ -64,6 +64,33 @@ def test_decode_matches_oracle(B, Hq, Hkv, D, S, C, lens):
     _check(_np(o), _np(lse), Or, LSEr, f"B{B} S{S} C{C}")
 
 
+# Query rows per KV head at the edges of the team sizes (one wave to 32 rows,
+# two to 64, four to 128, then groups), with ragged last tiles, empty caches,
+# few items over many teams (eight-way merge) and runs that cross items.
+TEAM_CASES = [
+    # B, Hq, Hkv, D, S, capacity, cache lengths
+    (1, 4, 1, 128, 4, 1600, [1531]),                     # 16 rows: one item, many runs
+    (2, 33, 1, 64, 1, 130, [129, 64]),                   # 33 rows: two waves, one row in the second
+    (3, 4, 2, 128, 32, 700, [700, 0, 33]),               # 64 rows, 32-key tiles
+    (2, 65, 1, 64, 1, 300, [257, 1]),                    # 65 rows: four waves, one of them empty
+    (24, 8, 2, 128, 32, 400, [(37 * i) % 401 for i in range(24)]),   # 128 rows, 64-key tiles
+    (2, 8, 2, 64, 36, 200, [191, 65]),                   # 144 rows: two groups of 96 and 48
+    (2, 4, 1, 128, 64, 150, [150, 3]),                   # 256 rows: two groups of 128
+    (300, 6, 1, 128, 16, 70, [i % 71 for i in range(300)]),          # 96 rows, more sequences than threads
+]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,S,C,lens", TEAM_CASES)
+def test_decode_teams_match_oracle(B, Hq, Hkv, D, S, C, lens):
+    """Tolerances as above (the arithmetic per row is the same in every team size)."""
+    print(f"[decode] teams B{B} H{Hq}/{Hkv} D{D} S{S} C{C}", flush=True)
+    q, kc, vc, kn, vn, cl = make_decode_inputs(B, Hq, Hkv, D, S, C, lens, seed=900 + Hq * S + C)
+    o, lse = bd_attn_decode_fwd(*(t.to(DEV) for t in (q, kc, vc, kn, vn, cl)))
+    torch.cuda.synchronize()
+    Or, LSEr = oracle.decode_forward(*(t.double().numpy() for t in (q, kc, vc, kn, vn)), lens)
+    _check(_np(o), _np(lse), Or, LSEr, f"teams B{B} G*S={Hq // Hkv * S} C{C}")
+
+
 def test_decode_cache_lengths_are_clamped():
     """Lengths beyond the capacity act as the capacity, negative ones as 0."""
     B, Hq, Hkv, D, S, C = 2, 4, 2, 64, 4, 96
