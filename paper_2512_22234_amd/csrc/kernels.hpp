@@ -239,7 +239,7 @@ hipError_t launch_decode(const DecodeShape& s, const void* Q, const void* Kc, co
 
 // Token log-probabilities through the LM head (H [N][Dm] x W [V][Dm]),
 // fused with their softmax.  Dm is a multiple of 256.
-constexpr int LCE_BK = 32;  // k per GEMM chunk
+constexpr int LCE_BK = 64;  // k per GEMM chunk
 struct LceShape {
   int N, V, Dm;
 };

@@ -14,12 +14,17 @@
 // The target logit of each token is one float32 dot product (merge and
 // one-hot kernels), so the tile epilogues carry no per-element target test.
 // The logits never reach HBM.  Every product is one GEMM kernel: 256 x 256
-// output tiles, four waves of 128 x 128, k in chunks of 32 through a
-// four-stage LDS ring (HBM/L2 -> LDS copies three chunks ahead), one
-// workgroup barrier per chunk placed mid-chunk so that the operand reads of
-// the next chunk overlap the MFMAs of the current one.  An operand tile is
-// either ROW (256 rows of 32 k values: the k index is contiguous in memory)
-// or TR (32 k rows of 256 values: the other index is contiguous), read with
+// output tiles, four waves of 128 x 128, k in chunks of 64 through LDS rings
+// (three stages on the A side, two on the B side, HBM/L2 -> LDS copies two
+// chunks ahead), one workgroup barrier per chunk, placed before its last MFMA
+// step so that the operand reads of the next chunk overlap that step's MFMAs.
+// Chunks of 64 make the rows of a ROW tile whole 128-byte cache lines: chunks
+// of 32 fetched every line of L2 twice (4096 x 151,936 x 4096: forward 4.54 ->
+// 3.83 ms, recompute 4.78 -> 4.01, dH 4.15 -> 3.66, dW 4.66 -> 4.11, 1240 to
+// 1390 TFLOP/s; a fourth 32-wide stage of lookahead alone changed nothing, and
+// 256 x 128 tiles at two workgroups per CU took 5.2 ms).  An operand tile is
+// either ROW (256 rows of 64 k values: the k index is contiguous in memory)
+// or TR (64 k rows of 256 values: the other index is contiguous), read with
 // row-slice or transposing LDS reads in the same k order.  Output rows are
 // the B side of the MFMA, so each lane holds four consecutive output columns
 // and the epilogues stage whole 512-byte rows through LDS.
@@ -37,15 +42,16 @@
 namespace bd {
 namespace {
 
-constexpr int TB = 256;               // output tile (both sides)
-constexpr int BK = LCE_BK;            // k per chunk
-constexpr int NST = 4;                // LDS ring stages
-constexpr uint32_t OPB = TB * BK * 2;  // bytes of one operand tile (16 KB)
-constexpr int RED_STRIDE = TB + 8;    // staging row stride (bf16) of the output tile: 528 bytes
+constexpr int TB = 256;                // output tile (both sides)
+constexpr int BK = LCE_BK;             // k per chunk
+constexpr int KS = BK / 16;            // MFMA k steps per chunk
+constexpr uint32_t OPB = TB * BK * 2;  // bytes of one operand tile (32 KB)
+constexpr int RED_STRIDE = TB + 8;     // staging row stride (bf16) of the output tile: 528 bytes
 
 // EPI_FWD_KEEP is EPI_FWD that also stores the float32 logits (a variant of
 // its own, so the plain forward's epilogue carries none of its registers)
-enum Epi { EPI_FWD = 0, EPI_REC = 1, EPI_STORE = 2, EPI_FWD_KEEP = 3 };
+// EPI_PART stores the float32 sums of one part of the k extent.
+enum Epi { EPI_FWD = 0, EPI_REC = 1, EPI_STORE = 2, EPI_FWD_KEEP = 3, EPI_PART = 4 };
 
 struct LceParams {
   const bf16* A;  // A-side source
@@ -55,6 +61,7 @@ struct LceParams {
   int Mcols, Nrows;  // output columns (A side) and rows (B side) that exist
   int K;             // k extent rounded up to BK (padding reads as zero)
   int nMT, nNT;      // tiles along the A and B sides
+  int ns;            // parts of the k extent (PART; else 1)
   // epilogue
   const int* targets;  // [N]
   const float* coef;   // [N]
@@ -67,10 +74,31 @@ struct LceParams {
   int V;               // vocabulary size (FWD/REC: valid A-side columns)
 };
 
-// Tile order: super-blocks of 4 (A side) x 8 (B side) tiles, dealt to the 8
-// XCDs in turn (workgroups are dispatched round-robin over the XCDs), so the
-// 32 workgroups an XCD runs at once share 4 A tiles and 8 B tiles in its L2.
+// Tile order: bands of GN tiles (B side), each cut into blocks of GM (A side)
+// x GN tiles, the last ones of each side smaller; the parts of a split k
+// extent one after another.  Every XCD takes one contiguous run of that order
+// (workgroups are dispatched round-robin over the XCDs), so the workgroups it
+// runs at once share few A and B tiles in its L2, and all XCDs have the same
+// number of tiles whatever the shape.
 constexpr int GM = 4, GN = 8;
+struct TilePos {
+  int split, mt, nt;
+};
+__device__ inline bool tile_of(int id, int nMT, int nNT, int ns, TilePos& t) {
+  const int nt1 = nMT * nNT, U = nt1 * ns;
+  const int x = id & 7, slot = id >> 3, q = U >> 3, r = U & 7;
+  if (slot >= q + (x < r)) return false;
+  const int u = x * q + imin(x, r) + slot;
+  t.split = u / nt1;
+  const int v = u - t.split * nt1;
+  const int band = v / (nMT * GN), b0 = band * GN, h = imin(GN, nNT - b0);
+  const int v2 = v - band * nMT * GN;
+  const int mg = v2 / (GM * h), m0 = mg * GM, w = imin(GM, nMT - m0);
+  const int v3 = v2 - mg * GM * h;
+  t.nt = b0 + v3 / w;
+  t.mt = m0 + v3 % w;
+  return true;
+}
 
 // Buffer resource built from values that are the same in every lane: taking
 // them through readfirstlane keeps the descriptor in scalar registers (a
@@ -85,55 +113,61 @@ __device__ inline __amdgpu_buffer_rsrc_t uniform_buffer(const void* base, size_t
 template <bool TR>
 struct OperandCopy;
 
-// ROW: 256 rows x 32 k (64-byte rows, swizzled); a wave copies 4 KB per chunk.
+// ROW: 256 rows x 64 k (128-byte rows, swizzled: whole cache lines, where rows
+// of 32 k would fetch every line twice); a wave copies 8 KB per chunk.
 template <>
 struct OperandCopy<false> {
-  uint32_t off[4];  // byte offset of this lane's 16 bytes for instruction u, within rows of stride ld
+  static constexpr int NI = 8;
+  uint32_t off[NI];  // byte offset of this lane's 16 bytes for instruction u, within rows of stride ld
   __device__ OperandCopy(int w, int lane, int ld) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < NI; ++u) {
       const int p = (u * 4 + w) * 64 + lane;  // 16-byte chunk of the LDS tile
-      const int r = p >> 2, c = (p & 3) ^ chunk_swizzle<BK>(r);
+      const int r = p >> 3, c = (p & 7) ^ chunk_swizzle<BK>(r);
       off[u] = (uint32_t)(2 * ((size_t)r * ld + c * 8));
     }
   }
-  // rows [r0, r0 + 256) of src (valid below ext), k columns [k0, k0 + 32); w: this wave (uniform)
+  // rows [r0, r0 + 256) of src (valid below ext), k columns [k0, k0 + 64); w: this wave (uniform)
   __device__ void issue(const bf16* src, int ld, int ext, int r0, int k0, char* dst, int w) const {
     const int rows = imin(TB, ext - r0);
-    const __amdgpu_buffer_rsrc_t rs = uniform_buffer(src + (size_t)r0 * ld, (size_t)imax(rows, 0) * ld * 2);
+    // (the descriptor starts at column k0 and ends with the last row)
+    const __amdgpu_buffer_rsrc_t rs =
+        uniform_buffer(src + (size_t)r0 * ld + k0, rows > 0 ? ((size_t)rows * ld - k0) * 2 : 0);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < NI; ++u)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + (u * 4 + w) * 1024),
-                                               16, (int)(off[u] + 2 * k0), 0, 0, 0);
+                                               16, (int)off[u], 0, 0, 0);
   }
 };
 
-// TR: 32 k rows x 256 columns, as two 32 x 128 sub-tiles (256-byte rows).
+// TR: 64 k rows x 256 columns, as two 64 x 128 sub-tiles (256-byte rows).
 template <>
 struct OperandCopy<true> {
-  uint32_t off[4];
+  static constexpr int NI = 8;
+  uint32_t off[NI];
   __device__ OperandCopy(int w, int lane, int ld) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int sub = u >> 1;
-      const int p = ((u & 1) * 4 + w) * 64 + lane;  // 16-byte chunk of the sub-tile
+    for (int u = 0; u < NI; ++u) {
+      const int sub = u >> 2;
+      const int p = ((u & 3) * 4 + w) * 64 + lane;  // 16-byte chunk of the sub-tile
       const int r = p >> 4, c = (p & 15) ^ chunk_swizzle<128>(r);
       off[u] = (uint32_t)(2 * ((size_t)r * ld + sub * 128 + c * 8));
     }
   }
-  // k rows [k0, k0 + 32) of src (valid below ext), columns [c0, c0 + 256); w: this wave (uniform)
+  // k rows [k0, k0 + 64) of src (valid below ext), columns [c0, c0 + 256); w: this wave (uniform)
   __device__ void issue(const bf16* src, int ld, int ext, int c0, int k0, char* dst, int w) const {
     const int rows = imin(BK, ext - k0);
-    const __amdgpu_buffer_rsrc_t rs = uniform_buffer(src + (size_t)k0 * ld + c0, (size_t)imax(rows, 0) * ld * 2);
+    const __amdgpu_buffer_rsrc_t rs =
+        uniform_buffer(src + (size_t)k0 * ld + c0, rows > 0 ? ((size_t)rows * ld - c0) * 2 : 0);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < NI; ++u)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rs, (__attribute__((address_space(3))) void*)(dst + (u >> 1) * (OPB / 2) + ((u & 1) * 4 + w) * 1024), 16,
+          rs, (__attribute__((address_space(3))) void*)(dst + (u >> 2) * (OPB / 2) + ((u & 3) * 4 + w) * 1024), 16,
           (int)off[u], 0, 0, 0);
   }
 };
 
-// MFMA operand of 32-block `blk` (0..7) of a side, k16 step s (0, 1) of the chunk.
+// MFMA operand of 32-block `blk` (0..7) of a side, k16 step s (0..3) of the chunk.
 struct OperandRead {
   uint32_t row_rel;     // ROW tiles
   uint32_t tr0, tr1;    // TR tiles (linear k order)
@@ -151,13 +185,17 @@ struct OperandRead {
   }
 };
 
+// Rings of operand tiles: three stages on the A side, whose tiles come from
+// HBM in most products, two on the B side (all of a CU's LDS).
+constexpr int NSA = 3, NSB = 2;
 struct LceSmem {
-  alignas(256) char a[NST][OPB];
-  alignas(256) char b[NST][OPB];
-  float2 red[2][TB];  // FWD: per token row, the two A-half waves' (max, sum)
+  alignas(256) char a[NSA * OPB];
+  alignas(256) char b[NSB * OPB];
 };
-// The output tile is staged over the ring once the k loop is done.
-static_assert(sizeof(LceSmem) >= TB * RED_STRIDE * 2, "staging fits in the ring");
+static_assert(sizeof(LceSmem) == 160 * 1024, "one workgroup per CU");
+// Once the k loop is done the rings hold the staged output tile, or (FWD) the
+// two A-half waves' (max, sum) per token row.
+static_assert(sizeof(LceSmem) >= TB * RED_STRIDE * 2 && sizeof(LceSmem) >= 2 * TB * sizeof(float2), "reuse fits");
 
 template <int EPI, bool ATR, bool BTR>
 __global__ __launch_bounds__(256, 1) void lce_gemm_kernel(LceParams p) {
@@ -168,23 +206,26 @@ __global__ __launch_bounds__(256, 1) void lce_gemm_kernel(LceParams p) {
   const int wa = w & 1, wb = w >> 1;  // this wave's 128-wide halves of the A and B sides
 
   // tile of this workgroup
-  const int id = blockIdx.x, xcd = id & 7, slot = id >> 3;
-  const int nBN = cdiv(p.nNT, GN);
-  const int blk = (slot / (GM * GN)) * 8 + xcd, within = slot % (GM * GN);
-  const int mt = (blk / nBN) * GM + within % GM, nt = (blk % nBN) * GN + within / GM;
-  if (mt >= p.nMT || nt >= p.nNT) return;
+  TilePos tp;
+  if (!tile_of(blockIdx.x, p.nMT, p.nNT, p.ns, tp)) return;
+  const int mt = tp.mt, nt = tp.nt;
   const int m0 = mt * TB, n0 = nt * TB;
 
   const OperandCopy<ATR> ca(w, lane, p.lda);
   const OperandCopy<BTR> cb(w, lane, p.ldb);
   const OperandRead rd(lane);
-  auto issue = [&](int kc, char* da, char* db) {
-    const int k0 = kc * BK;
-    ca.issue(p.A, p.lda, p.a_ext, m0, k0, da, w);
-    cb.issue(p.B, p.ldb, p.b_ext, n0, k0, db, w);
+  const int nkt = p.K / BK;
+  // k chunks of this part: [kc0, kc0 + nk)
+  const int kc0 = EPI == EPI_PART ? (int)((long long)nkt * tp.split / p.ns) : 0;
+  const int nk = EPI == EPI_PART ? (int)((long long)nkt * (tp.split + 1) / p.ns) - kc0 : nkt;
+  // chunk kc (the last one again past the end, into stages nothing reads any more)
+  auto issue_a = [&](int kc, char* dst) __attribute__((always_inline)) {
+    ca.issue(p.A, p.lda, p.a_ext, m0, (kc0 + imin(kc, nk - 1)) * BK, dst, w);
   };
-  const int nk = p.K / BK;
-  constexpr int NI = 8;  // copy instructions per wave per chunk
+  auto issue_b = [&](int kc, char* dst) __attribute__((always_inline)) {
+    cb.issue(p.B, p.ldb, p.b_ext, n0, (kc0 + imin(kc, nk - 1)) * BK, dst, w);
+  };
+  constexpr int NA = decltype(ca)::NI;  // copy instructions per wave per A tile
 
   f32x16 acc[4][4];
 #pragma unroll
@@ -194,10 +235,12 @@ __global__ __launch_bounds__(256, 1) void lce_gemm_kernel(LceParams p) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-#pragma unroll
-  for (int c = 0; c < NST - 1; ++c) issue(imin(c, nk - 1), sm.a[c], sm.b[c]);
-  wait_global_loads_but<(NST - 2) * NI>();  // chunk 0 has landed
-  __syncthreads();
+  issue_a(0, sm.a);
+  issue_b(0, sm.b);
+  issue_a(1, sm.a + OPB);
+  issue_b(1, sm.b + OPB);
+  wait_global_loads_but<2 * NA>();  // chunk 0 has landed (this wave's part)
+  barrier_lds_only();
 
   bf16x8 a0[4], b0[4], a1[4], b1[4];
   auto read = [&](const char* ta, const char* tb, int s, bf16x8* a, bf16x8* b) __attribute__((always_inline)) {
@@ -213,45 +256,60 @@ __global__ __launch_bounds__(256, 1) void lce_gemm_kernel(LceParams p) {
       for (int j = 0; j < 4; ++j) acc[i][j] = mfma32(a[i], b[j], acc[i][j]);
   };
   // LDS reads per k16 step: 8 for ROW/ROW, up to 16 for TR/TR (a transposing
-  // operand takes two 8-byte reads)
+  // operand takes two 8-byte reads).  One read beside each MFMA and, in the
+  // steps that copy, one copy beside every second one.
   constexpr int RPS = (ATR ? 8 : 4) + (BTR ? 8 : 4);
-  // Chunk kc, step 0's operands already in (a0, b0):
-  //   step 0 MFMAs beside the reads of step 1;
-  //   wait for chunk kc + 1, barrier (all copies in; all waves done with chunk kc - 1);
-  //   copy chunk kc + 3 into chunk kc - 1's stage;
-  //   step 1 MFMAs beside the reads of chunk kc + 1's step 0.
-  auto half1 = [&](const char* __restrict__ ta, const char* __restrict__ tb) __attribute__((always_inline)) {
+  auto schedule = [&](auto copies) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (q < RPS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if (decltype(copies)::value && (q & 1) == 0) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Chunk kc (stages ta, tb), step 0's operands already in (a0, b0).  Every
+  // step's MFMAs run beside the operand reads of the next step:
+  //   step 0 also copies A of chunk kc + 2 into wa_ (chunk kc - 1's stage);
+  //   after step 2 all operands of chunk kc have been read: wait for chunk
+  //   kc + 1, barrier (all of it is in, all waves have read chunk kc);
+  //   step 3 reads chunk kc + 1's step 0 and copies B of chunk kc + 2 into
+  //   chunk kc's stage.
+  auto steps012 = [&](const char* __restrict__ ta, const char* __restrict__ tb, char* __restrict__ wa_, int kc)
+                      __attribute__((always_inline)) {
+    issue_a(kc + 2, wa_);
     read(ta, tb, 1, a1, b1);
     mm(a0, b0);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (q < RPS) __builtin_amdgcn_sched_group_barrier(0x100, RPS > 16 ? 2 : 1, 0);
-    }
+    schedule(Flag<true>());
+    read(ta, tb, 2, a0, b0);
+    mm(a1, b1);
+    schedule(Flag<false>());
+    read(ta, tb, 3, a1, b1);
+    mm(a0, b0);
+    schedule(Flag<false>());
   };
-  auto half2 = [&](const char* __restrict__ ta, const char* __restrict__ tb, char* __restrict__ wa_, char* __restrict__ wb_,
-                   int kc) __attribute__((always_inline)) {
-    issue(imin(kc + NST - 1, nk - 1), wa_, wb_);
+  auto step3 = [&](const char* __restrict__ ta, const char* __restrict__ tb, char* __restrict__ wb_, int kc)
+                   __attribute__((always_inline)) {
+    issue_b(kc + 2, wb_);
     read(ta, tb, 0, a0, b0);
     mm(a1, b1);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (q < RPS) __builtin_amdgcn_sched_group_barrier(0x100, RPS > 16 ? 2 : 1, 0);
-      if (q < NI) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    }
+    schedule(Flag<true>());
   };
-  read(sm.a[0], sm.b[0], 0, a0, b0);
+  read(sm.a, sm.b, 0, a0, b0);
+  uint32_t sa = 0, sb = 0;  // ring offsets of chunk kc
   for (int kc = 0; kc < nk; ++kc) {
-    const int st = kc % NST, s1 = (kc + 1) % NST, sw = (kc + NST - 1) % NST;
-    half1(sm.a[st], sm.b[st]);
+    const uint32_t sa1 = sa == (NSA - 1) * OPB ? 0u : sa + OPB, sa2 = sa1 == (NSA - 1) * OPB ? 0u : sa1 + OPB;
+    const uint32_t sb1 = OPB - sb;
+    steps012(sm.a + sa, sm.b + sb, sm.a + sa2, kc);
     compute_fence();
-    wait_global_loads_but<(NST - 3) * NI>();  // chunk kc + 1 has landed (this wave's part)
+    wait_global_loads_but<NA>();  // all but A of chunk kc + 2 (this wave's part)
     barrier_lds_only();
-    half2(sm.a[s1], sm.b[s1], sm.a[sw], sm.b[sw], kc);
+    step3(sm.a + sa1, sm.b + sb1, sm.b + sb, kc);
     compute_fence();
+    sa = sa1;
+    sb = sb1;
   }
-  wait_global_loads();  // the last (repeated) copies, before the ring is reused
+  wait_global_loads();  // the last (repeated) copies, before the rings are reused
   __syncthreads();
 
   // acc[i][j][4 i4 + jj]: A-side column  m0 + 128 wa + 32 i + 8 i4 + 4 g2 + jj,
@@ -259,6 +317,7 @@ __global__ __launch_bounds__(256, 1) void lce_gemm_kernel(LceParams p) {
   // Columns past the vocabulary exist only in the last vocabulary tile.
   const bool partial_cols = m0 + TB > p.V;
   if constexpr (EPI == EPI_FWD || EPI == EPI_FWD_KEEP) {
+    float2* const red = reinterpret_cast<float2*>(&sm);  // [A half][token row]
     // per token: max and sum of exp over this tile's vocabulary columns (log2
     // units).  Every tile takes the masked path: a branch between a masked and
     // an unmasked copy makes the compiler move all 256 accumulators into VGPRs
@@ -285,7 +344,7 @@ __global__ __launch_bounds__(256, 1) void lce_gemm_kernel(LceParams p) {
           for (int e = 0; e < 16; ++e) sum += fast_exp2(score(i, e) - mx);  // exp2(-inf) = 0
       }
       sum = halves_sum(sum);
-      if (g2 == 0) sm.red[wa][128 * wb + 32 * j + l32] = float2{mx, sum};
+      if (g2 == 0) red[wa * TB + 128 * wb + 32 * j + l32] = float2{mx, sum};
     }
     if constexpr (EPI == EPI_FWD_KEEP) {
       // the logits for the backward pass (columns past V hold the zero rows'
@@ -308,10 +367,26 @@ __global__ __launch_bounds__(256, 1) void lce_gemm_kernel(LceParams p) {
     // two halves of the vocabulary tile -> one partial per token
     const int n = n0 + tid;
     if (n < p.Nrows) {
-      const float2 x = sm.red[0][tid], y = sm.red[1][tid];
+      const float2 x = red[tid], y = red[TB + tid];
       const float M = fmaxf(x.x, y.x);  // finite: every tile holds at least one vocabulary row
       const float S = x.y * fast_exp2(x.x - M) + y.y * fast_exp2(y.x - M);
       *reinterpret_cast<float2*>(p.part + 2 * ((size_t)n * p.nMT + mt)) = float2{M, S};
+    }
+  } else if constexpr (EPI == EPI_PART) {
+    // float32 sums of this part, [split][Nrows][ldl]
+    float* const part = p.logits + (size_t)tp.split * p.Nrows * p.ldl;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int n = n0 + 128 * wb + 32 * j + l32;
+      if (n < p.Nrows) {
+        float* lr = part + (size_t)n * p.ldl + m0 + 128 * wa + 4 * g2;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int i4 = 0; i4 < 4; ++i4)
+            *reinterpret_cast<f32x4*>(lr + 32 * i + 8 * i4) =
+                f32x4{acc[i][j][4 * i4], acc[i][j][4 * i4 + 1], acc[i][j][4 * i4 + 2], acc[i][j][4 * i4 + 3]};
+      }
     }
   } else {
     // stage the bf16 output tile, rows = B side, 4 consecutive columns per lane and (i, i4)
@@ -490,11 +565,45 @@ __global__ __launch_bounds__(256) void lce_objective_kernel(const float* logp, c
   dlogp[n] = -w * (ds - beta * dkl);
 }
 
+// Parts of the k extent (the vocabulary) of the dH product: it has few output
+// tiles (Dm / 256 x N / 256) and a long k loop, so with one part the last round
+// of workgroups leaves most of the chip idle.  The number of parts minimises
+// rounds x chunks per part (each round starts and ends its tiles for about 16
+// chunks' time), with at least 32 chunks a part and the parts' float32 sums
+// within dW, where they wait: 2 ns N <= V.  N = 777, Dm = 4096, V = 151,936: 64
+// tiles, four parts, 3.12 -> 0.91 ms (and 10 us to add the parts).
+inline int dh_parts(const LceShape& s) {
+  const long long tiles = (long long)(s.Dm / TB) * cdiv(s.N, TB);
+  const long long slots = 256;
+  const int nk = lce_vocab_tiles(s) * (256 / BK);
+  int best = 1;
+  double cost = 1e30;
+  for (int ns = 1; ns <= 32; ++ns) {
+    if (ns > 1 && ((long long)2 * ns * s.N > s.V || nk / ns < 32)) break;
+    // rounds of workgroups, each of nk / ns chunks (and about 16 more for its start and end)
+    const double c = (double)((tiles * ns + slots - 1) / slots) * ((double)nk / ns + 16 + (ns > 1 ? 4 : 0));
+    if (c < cost * 0.98) {
+      cost = c;
+      best = ns;
+    }
+  }
+  return best;
+}
+
+// The parts' float32 sums added in part order, as bf16.  One thread per 4 values.
+__global__ __launch_bounds__(256) void lce_sum_parts_kernel(const float* part, int ns, size_t n4, bf16* out) {
+  const size_t id = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (id >= n4) return;
+  f32x4 t = *reinterpret_cast<const f32x4*>(part + 4 * id);
+  for (int s = 1; s < ns; ++s) t += *reinterpret_cast<const f32x4*>(part + 4 * (s * n4 + id));
+  st_bf16x4(out + 4 * id, t[0], t[1], t[2], t[3]);
+}
+
 template <int EPI, bool ATR, bool BTR>
-hipError_t launch_gemm(const LceParams& p, hipStream_t st) {
-  const int nBM = cdiv(p.nMT, GM), nBN = cdiv(p.nNT, GN);
-  const int grid = cdiv(nBM * nBN, 8) * 8 * GM * GN;
-  hipLaunchKernelGGL((lce_gemm_kernel<EPI, ATR, BTR>), dim3(grid), dim3(256), 0, st, p);
+hipError_t launch_gemm(LceParams p, int rows, hipStream_t st) {
+  p.nNT = cdiv(rows, TB);
+  const long long U = (long long)p.nMT * p.nNT * p.ns;
+  hipLaunchKernelGGL((lce_gemm_kernel<EPI, ATR, BTR>), dim3((unsigned)((U + 7) / 8 * 8)), dim3(256), 0, st, p);
   return hipGetLastError();
 }
 
@@ -512,15 +621,15 @@ hipError_t launch_lce_fwd(const LceShape& s, const void* H, const void* W, const
   p.Nrows = s.N;
   p.K = s.Dm;
   p.nMT = lce_vocab_tiles(s);
-  p.nNT = cdiv(s.N, TB);
+  p.ns = 1;
   p.targets = targets;
   char* w = static_cast<char*>(ws);
   p.part = reinterpret_cast<float*>(w + lce_fwd_part_offset(s));
   p.logits = logits;
   p.ldl = lce_vocab_tiles(s) * TB;
   p.V = s.V;
-  hipError_t e = logits != nullptr ? launch_gemm<EPI_FWD_KEEP, false, false>(p, st)
-                                    : launch_gemm<EPI_FWD, false, false>(p, st);
+  hipError_t e = logits != nullptr ? launch_gemm<EPI_FWD_KEEP, false, false>(p, s.N, st)
+                                    : launch_gemm<EPI_FWD, false, false>(p, s.N, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(lce_merge_kernel, dim3(cdiv(s.N, 4)), dim3(256), 0, st, p.part, p.B, p.A, targets, s.N, p.nMT,
                      s.V, s.Dm, lse, logp);
@@ -550,7 +659,7 @@ hipError_t launch_lce_bwd(const LceShape& s, const void* H, const void* W, const
   p.Nrows = s.N;
   p.K = s.Dm;
   p.nMT = lce_vocab_tiles(s);
-  p.nNT = cdiv(s.N, TB);
+  p.ns = 1;
   p.targets = targets;
   p.coef = coef;
   p.lse = lse;
@@ -564,7 +673,7 @@ hipError_t launch_lce_bwd(const LceShape& s, const void* H, const void* W, const
                        targets, lse, coef, s.N, s.V, Vp, G);
     e = hipGetLastError();
   } else {
-    e = launch_gemm<EPI_REC, false, false>(p, st);
+    e = launch_gemm<EPI_REC, false, false>(p, s.N, st);
   }
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(lce_onehot_kernel, dim3(cdiv(s.N, 4)), dim3(256), 0, st, p.B, p.A, targets, lse, coef, s.N,
@@ -583,10 +692,22 @@ hipError_t launch_lce_bwd(const LceShape& s, const void* H, const void* W, const
   q.Nrows = s.N;
   q.K = Vp;
   q.nMT = s.Dm / TB;
-  q.nNT = cdiv(s.N, TB);
   q.C = static_cast<bf16*>(dH);
   q.ldc = s.Dm;
-  e = launch_gemm<EPI_STORE, true, false>(q, st);
+  q.ns = dh_parts(s);
+  if (q.ns > 1) {
+    // the parts' sums lie in dW, which the next product overwrites
+    q.logits = static_cast<float*>(dW);
+    q.ldl = s.Dm;
+    e = launch_gemm<EPI_PART, true, false>(q, s.N, st);
+    if (e != hipSuccess) return e;
+    const size_t n4 = (size_t)s.N * s.Dm / 4;
+    hipLaunchKernelGGL(lce_sum_parts_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st,
+                       static_cast<const float*>(dW), q.ns, n4, static_cast<bf16*>(dH));
+    e = hipGetLastError();
+  } else {
+    e = launch_gemm<EPI_STORE, true, false>(q, s.N, st);
+  }
   if (e != hipSuccess) return e;
   // dW[v][d] = sum_n G[n][v] H[n][d]
   LceParams r{};
@@ -600,10 +721,10 @@ hipError_t launch_lce_bwd(const LceShape& s, const void* H, const void* W, const
   r.Nrows = s.V;
   r.K = cdiv(s.N, BK) * BK;
   r.nMT = s.Dm / TB;
-  r.nNT = lce_vocab_tiles(s);
+  r.ns = 1;
   r.C = static_cast<bf16*>(dW);
   r.ldc = s.Dm;
-  return launch_gemm<EPI_STORE, true, true>(r, st);
+  return launch_gemm<EPI_STORE, true, true>(r, s.V, st);
 }
 
 }  // namespace bd

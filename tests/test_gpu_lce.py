@@ -67,6 +67,14 @@ def test_lce_matches_oracle(N, V, Dm):
     assert np.all(_np(logp)[unscored] == 0) and np.all(_np(dh)[unscored] == 0)
 
 
+# dH in parts of the vocabulary (few output tiles, at least 2048 vocabulary
+# rows a part): two parts, four over two ragged position tiles, nineteen; and just
+# too small a vocabulary for two.
+@pytest.mark.parametrize("N,V,Dm", [(5, 5000, 256), (300, 9000, 512), (33, 40001, 256), (70, 4095, 256)])
+def test_lce_split_vocabulary_matches_oracle(N, V, Dm):
+    test_lce_matches_oracle(N, V, Dm)
+
+
 @pytest.mark.parametrize("N,V,Dm", [(100, 1000, 256), (513, 2048, 768)])
 def test_lce_kept_logits_match_recompute(N, V, Dm):
     """The backward from kept logits agrees with the recomputing one and with
