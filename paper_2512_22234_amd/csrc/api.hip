@@ -52,6 +52,9 @@ Layout make_layout(const bd::Shape& s, int dtype, bool bwd) {
     off += align256(bd::dkdv_pair_ints(s.B, s.Hkv, s.L) * 4);
   }
   if (dtype == BD_ATTN_FP32) {
+    // bf16 copies of the inputs.  (The forward's o and dq, dk, dv are room that
+    // nothing uses: the kernels write float32 results themselves, and the size
+    // stays what callers have been told to allocate.)
     w.q = off; off += align256(nq * 2);
     w.k = off; off += align256(nk * 2);
     w.v = off; off += align256(nk * 2);
@@ -97,6 +100,7 @@ int validate(int B, int L, int S, int Hq, int Hkv, int D, float scale, int dtype
   s.G = Hq / Hkv;
   s.scale = scale > 0.f ? scale : 1.0f / std::sqrt((float)D);
   s.seq = bd::SeqLayout{nullptr, 0};
+  s.out32 = dtype == BD_ATTN_FP32;
   return BD_ATTN_OK;
 }
 
@@ -125,6 +129,7 @@ int validate_varlen(const int32_t* cu, int n_seqs, int total_L, int max_L, int S
   s.G = Hq / Hkv;
   s.scale = scale > 0.f ? scale : 1.0f / std::sqrt((float)D);
   s.seq = bd::SeqLayout{cu, total_L};
+  s.out32 = dtype == BD_ATTN_FP32;
   return BD_ATTN_OK;
 }
 
@@ -594,8 +599,7 @@ int bd_lce_objective(const float* logp, const float* logp_old, const float* logp
 
 const char* bd_attn_stage_names(int for_bwd, int dtype) {
   if (dtype == BD_ATTN_FP32)
-    return for_bwd ? "cast_q,cast_k,cast_v,cast_o,cast_do,bwd_dq,bwd_dkdv,cast_dq,cast_dk,cast_dv"
-                   : "cast_q,cast_k,cast_v,fwd,cast_o";
+    return for_bwd ? "cast,bwd_dq,bwd_dkdv" : "cast,fwd";
   return for_bwd ? "bwd_dq,bwd_dkdv" : "fwd";
 }
 
@@ -625,18 +629,22 @@ int fwd_impl(const bd::Shape& s, const void* Q, const void* K, const void* V, in
   (void)hipGetLastError();  // clear a stale error so it is not reported as ours
   char* wb = static_cast<char*>(ws);
   const void *q = Q, *k = K, *v = V;
-  void* o = O;
   if (dtype == BD_ATTN_FP32) {
-    BD_TRY(bd::launch_cast_f32_to_bf16(static_cast<const float*>(Q), wb + w.q, nq, stream, marks.next()));
-    BD_TRY(bd::launch_cast_f32_to_bf16(static_cast<const float*>(K), wb + w.k, nk, stream, marks.next()));
-    BD_TRY(bd::launch_cast_f32_to_bf16(static_cast<const float*>(V), wb + w.v, nk, stream, marks.next()));
+    bd::CastList c{};
+    c.count = 3;
+    const void* src[] = {Q, K, V};
+    const size_t at[] = {w.q, w.k, w.v}, n[] = {nq, nk, nk};
+    for (int i = 0; i < 3; ++i) {
+      c.src[i] = src[i];
+      c.dst[i] = wb + at[i];
+      c.n[i] = n[i];
+    }
+    BD_TRY(bd::launch_cast_f32_to_bf16(c, stream, marks.next()));
     q = wb + w.q;
     k = wb + w.k;
     v = wb + w.v;
-    o = wb + w.o;
   }
-  BD_TRY(bd::launch_fwd(s, q, k, v, o, LSE, stream, marks.next()));
-  if (dtype == BD_ATTN_FP32) BD_TRY(bd::launch_cast_bf16_to_f32(o, static_cast<float*>(O), nq, stream, marks.next()));
+  BD_TRY(bd::launch_fwd(s, q, k, v, O, LSE, stream, marks.next()));
   return BD_ATTN_OK;
 }
 
@@ -666,32 +674,28 @@ int bwd_impl(const bd::Shape& s, const void* dO, const void* Q, const void* K, c
   (void)hipGetLastError();
   char* wb = static_cast<char*>(ws);
   const void *q = Q, *k = K, *v = V, *o = O, *g = dO;
-  void *dq = dQ, *dk = dK, *dv = dV;
   if (dtype == BD_ATTN_FP32) {
-    BD_TRY(bd::launch_cast_f32_to_bf16(static_cast<const float*>(Q), wb + w.q, nq, stream, marks.next()));
-    BD_TRY(bd::launch_cast_f32_to_bf16(static_cast<const float*>(K), wb + w.k, nk, stream, marks.next()));
-    BD_TRY(bd::launch_cast_f32_to_bf16(static_cast<const float*>(V), wb + w.v, nk, stream, marks.next()));
-    BD_TRY(bd::launch_cast_f32_to_bf16(static_cast<const float*>(O), wb + w.o, nq, stream, marks.next()));
-    BD_TRY(bd::launch_cast_f32_to_bf16(static_cast<const float*>(dO), wb + w.dout, nq, stream, marks.next()));
+    bd::CastList c{};
+    c.count = 5;
+    const void* src[] = {Q, K, V, O, dO};
+    const size_t at[] = {w.q, w.k, w.v, w.o, w.dout}, n[] = {nq, nk, nk, nq, nq};
+    for (int i = 0; i < 5; ++i) {
+      c.src[i] = src[i];
+      c.dst[i] = wb + at[i];
+      c.n[i] = n[i];
+    }
+    BD_TRY(bd::launch_cast_f32_to_bf16(c, stream, marks.next()));
     q = wb + w.q;
     k = wb + w.k;
     v = wb + w.v;
     o = wb + w.o;
     g = wb + w.dout;
-    dq = wb + w.dq;
-    dk = wb + w.dk;
-    dv = wb + w.dv;
   }
   float* rs = reinterpret_cast<float*>(wb + w.rs);
   float* part = reinterpret_cast<float*>(wb + w.part);
   int* pair = reinterpret_cast<int*>(wb + w.pair);
-  BD_TRY(bd::launch_bwd_dq(s, q, k, v, g, o, LSE, rs, pair, dq, stream, marks.next()));
-  BD_TRY(bd::launch_bwd_dkdv(s, q, k, v, g, rs, dk, dv, part, pair, stream, marks.next()));
-  if (dtype == BD_ATTN_FP32) {
-    BD_TRY(bd::launch_cast_bf16_to_f32(dq, static_cast<float*>(dQ), nq, stream, marks.next()));
-    BD_TRY(bd::launch_cast_bf16_to_f32(dk, static_cast<float*>(dK), nk, stream, marks.next()));
-    BD_TRY(bd::launch_cast_bf16_to_f32(dv, static_cast<float*>(dV), nk, stream, marks.next()));
-  }
+  BD_TRY(bd::launch_bwd_dq(s, q, k, v, g, o, LSE, rs, pair, dQ, stream, marks.next()));
+  BD_TRY(bd::launch_bwd_dkdv(s, q, k, v, g, rs, dK, dV, part, pair, stream, marks.next()));
   return BD_ATTN_OK;
 }
 

@@ -46,8 +46,8 @@ struct DkvParams {
   const bf16* V;
   const bf16* dO;
   const float* rs;  // (lse2, delta) per query row
-  bf16* dK;
-  bf16* dV;
+  void* dK;  // bf16, or float32 (F32)
+  void* dV;
   float* part;  // [nsplit - 1 arrival slots][tile slots][4 consumer waves][32 x 16 bytes per lane]: unscaled sums of the parts of a clean key tile's walk that did not finish last
   int* pair;    // per (clean key tile, key group): DKV_PAIR_INTS counters (arrivals, published, slot owners), zeroed by the dq kernel
   SeqLayout seq;
@@ -101,7 +101,7 @@ struct DkvSmem {
 // copies issued in a step stay in flight across it.  In step t the query-tile buffers
 // hold tiles t - 1 (consumer), t and t + 1 (producer), t + 2 (landed or
 // landing) and t + 3 (being copied); the P/dS buffers steps t and t - 1.
-template <int D, int NSPLIT>
+template <int D, int NSPLIT, bool F32>
 __global__ __launch_bounds__(512, 1) void dkdv_kernel(DkvParams p) {
   constexpr int BM = DKV_BM, BN = DKV_BN;
   constexpr int DS = D / 16, DB = D / 32;
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(512, 1) void dkdv_kernel(DkvParams p) {
     wait_global_loads();  // no copy may still be writing LDS when the workgroup ends
 
     const float sc = isdk ? p.scale : 1.f;
-    bf16* const outp = isdk ? p.dK : p.dV;
+    void* const outp = isdk ? p.dK : p.dV;
     const size_t orow = khead + kh * L;  // first row of this KV head's half
     if (clean) {
       // The parts of this key tile's walk meet here, per consumer wave.  Each
@@ -578,11 +578,11 @@ __global__ __launch_bounds__(512, 1) void dkdv_kernel(DkvParams p) {
         for (int ks = 0; ks < 2; ++ks) {
           const int key = kc0 + 32 * ks + l32;
           if (key < k1) {
-            bf16* op = outp + (orow + key) * D + 4 * g2;
+            const size_t op = (orow + key) * D + 4 * g2;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
-              for (int i = 0; i < 4; ++i) st_bf16x4(op + db * 32 + 8 * i, nan, nan, nan, nan);
+              for (int i = 0; i < 4; ++i) st_out4<F32>(outp, op + db * 32 + 8 * i, nan, nan, nan, nan);
           }
         }
         return;
@@ -605,7 +605,8 @@ __global__ __launch_bounds__(512, 1) void dkdv_kernel(DkvParams p) {
       // are dropped, so no branch separates the loads of one group of
       // accumulator quads from the next and the loads can be issued together.
       const __amdgpu_buffer_rsrc_t ob =
-          make_buffer(outp + (orow + kc0) * D, (uint32_t)(imax(0, imin(BN / 2, k1 - kc0)) * D * 2));
+          make_buffer(static_cast<char*>(outp) + (((orow + kc0) * D) << (1 + F32)),
+                      (uint32_t)((imax(0, imin(BN / 2, k1 - kc0)) * D) << (1 + F32)));
       // groups of GQ accumulator quads: the other parts' sums of a group are
       // loaded together (nsplit - 1 of them per quad)
       constexpr int GQ = nsplit == 2 ? 8 : 4;
@@ -632,8 +633,13 @@ __global__ __launch_bounds__(512, 1) void dkdv_kernel(DkvParams p) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[e] = (bf16)(tot[e] * sc);
           typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), ob,
-                                                (uint32_t)(((32 * ks + l32) * D + 32 * db + 8 * i + 4 * g2) * 2), 0, 0);
+          const uint32_t oat = (uint32_t)((32 * ks + l32) * D + 32 * db + 8 * i + 4 * g2);
+          if constexpr (F32) {
+            const f32x4 of = {(float)o[0], (float)o[1], (float)o[2], (float)o[3]};
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, of), ob, 4 * oat, 0, 0);
+          } else {
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), ob, 2 * oat, 0, 0);
+          }
         }
       }
     } else {
@@ -641,12 +647,12 @@ __global__ __launch_bounds__(512, 1) void dkdv_kernel(DkvParams p) {
       for (int ks = 0; ks < 2; ++ks) {
         const int key = kc0 + 32 * ks + l32;
         if (key < k1) {
-          bf16* op = outp + (orow + key) * D + 4 * g2;
+          const size_t op = (orow + key) * D + 4 * g2;
 #pragma unroll
           for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-              st_bf16x4(op + db * 32 + 8 * i, acc[ks][db][4 * i] * sc, acc[ks][db][4 * i + 1] * sc,
+              st_out4<F32>(outp, op + db * 32 + 8 * i, acc[ks][db][4 * i] * sc, acc[ks][db][4 * i + 1] * sc,
                         acc[ks][db][4 * i + 2] * sc, acc[ks][db][4 * i + 3] * sc);
         }
       }
@@ -665,7 +671,7 @@ struct DqParams {
   float* rs;  // out: (lse2, delta) per query row, for the dK/dV kernel
   int* pair;  // dK/dV pairing counters, cleared here
   int npair;
-  bf16* dQ;
+  void* dQ;  // bf16, or float32 (F32)
   SeqLayout seq;
   int L, S, Hq, Hkv, G, nQT, nbh;
   float c;
@@ -680,7 +686,7 @@ struct DqSmem {
   bf16 v[2][BN * D];  // byte offset (2 + buf) * TILE
 };
 
-template <int D>
+template <int D, bool F32>
 __global__ __launch_bounds__(256, 2) void dq_kernel(DqParams p) {
   constexpr int BM = DQ_BM, BN = DQ_BN;
   constexpr int DS = D / 16, DB = D / 32, KB = BN / 32, PC = BN / 16;
@@ -891,13 +897,13 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqParams p) {
   }
 
   if (qvalid) {
-    bf16* dqp = p.dQ + qrow * D + 4 * g2;
+    const size_t dqp = qrow * D + 4 * g2;
     const float sc = p.scale;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        st_bf16x4(dqp + db * 32 + 8 * i, dqacc[db][4 * i] * sc, dqacc[db][4 * i + 1] * sc,
+        st_out4<F32>(p.dQ, dqp + db * 32 + 8 * i, dqacc[db][4 * i] * sc, dqacc[db][4 * i + 1] * sc,
                   dqacc[db][4 * i + 2] * sc, dqacc[db][4 * i + 3] * sc);
   }
 }
@@ -912,8 +918,8 @@ hipError_t launch_dkdv_d(const Shape& s, const void* Q, const void* K, const voi
   p.V = static_cast<const bf16*>(V);
   p.dO = static_cast<const bf16*>(dO);
   p.rs = rs;
-  p.dK = static_cast<bf16*>(dK);
-  p.dV = static_cast<bf16*>(dV);
+  p.dK = dK;
+  p.dV = dV;
   p.part = part;
   p.pair = pair;
   p.seq = s.seq;
@@ -930,11 +936,11 @@ hipError_t launch_dkdv_d(const Shape& s, const void* Q, const void* K, const voi
   // each clean key tile's walk in 2 or 4 parts, then the noisy key tiles
   // (packed sequences: grid sized by a bound on the key tiles of all sequences)
   const int rows = s.seq.cu ? packed_rows_bound(s.seq.T, s.B, s.L, DKV_BN) : p.nKT * s.B;
-  if (dkdv_nsplit(s) == 4) {
-    hipExtLaunchKernelGGL((dkdv_kernel<D, 4>), dim3(5 * rows * s.Hkv), dim3(512), 0, st, ev.start, ev.stop, 0, p);
-  } else {
-    hipExtLaunchKernelGGL((dkdv_kernel<D, 2>), dim3(3 * rows * s.Hkv), dim3(512), 0, st, ev.start, ev.stop, 0, p);
-  }
+  const int nsplit = dkdv_nsplit(s);
+  const dim3 grid((nsplit + 1) * rows * s.Hkv), block(512);
+  auto launch = [&](auto kernel) { hipExtLaunchKernelGGL(kernel, grid, block, 0, st, ev.start, ev.stop, 0, p); };
+  if (nsplit == 4) s.out32 ? launch(dkdv_kernel<D, 4, true>) : launch(dkdv_kernel<D, 4, false>);
+  else s.out32 ? launch(dkdv_kernel<D, 2, true>) : launch(dkdv_kernel<D, 2, false>);
   return hipGetLastError();
 }
 
@@ -952,7 +958,7 @@ hipError_t launch_dq_d(const Shape& s, const void* Q, const void* K, const void*
   p.pair = pair;
   p.npair = (int)dkdv_pair_ints(s.B, s.Hkv, s.L);
   p.seq = s.seq;
-  p.dQ = static_cast<bf16*>(dQ);
+  p.dQ = dQ;
   p.L = s.L;
   p.S = s.S;
   p.Hq = s.Hq;
@@ -963,7 +969,8 @@ hipError_t launch_dq_d(const Shape& s, const void* Q, const void* K, const void*
   p.c = s.scale * LOG2E;
   p.scale = s.scale;
   const dim3 grid(2 * p.nQT * p.nbh);
-  hipExtLaunchKernelGGL(dq_kernel<D>, grid, dim3(256), 0, st, ev.start, ev.stop, 0, p);
+  if (s.out32) hipExtLaunchKernelGGL((dq_kernel<D, true>), grid, dim3(256), 0, st, ev.start, ev.stop, 0, p);
+  else hipExtLaunchKernelGGL((dq_kernel<D, false>), grid, dim3(256), 0, st, ev.start, ev.stop, 0, p);
   return hipGetLastError();
 }
 

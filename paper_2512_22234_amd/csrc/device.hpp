@@ -322,6 +322,18 @@ __device__ inline void st_bf16x4(bf16* p, float a, float b, float c, float d) {
   *reinterpret_cast<bf16x4*>(p) = v;
 }
 
+// Store four consecutive results at element `at` of an output array, rounded to
+// bf16: as bf16, or widened to float32 (the float32 interface; what a separate
+// cast kernel would write).
+template <bool F32>
+__device__ inline void st_out4(void* out, size_t at, float a, float b, float c, float d) {
+  if constexpr (F32) {
+    *reinterpret_cast<f32x4*>(static_cast<float*>(out) + at) = f32x4{(float)(bf16)a, (float)(bf16)b, (float)(bf16)c, (float)(bf16)d};
+  } else {
+    st_bf16x4(static_cast<bf16*>(out) + at, a, b, c, d);
+  }
+}
+
 // Combine a per-lane value over the two half-waves (lanes l and l + 32 hold
 // the two halves of one row's keys or features) with v_permlane32_swap.
 __device__ inline float halves_max(float x) {

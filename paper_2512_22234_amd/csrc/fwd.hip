@@ -27,7 +27,7 @@ struct FwdParams {
   const bf16* Q;
   const bf16* K;
   const bf16* V;
-  bf16* O;
+  void* O;   // bf16, or float32 (F32)
   float* LSE;
   SeqLayout seq;
   int L, S, Hq, Hkv, G, nQT, nbh;  // L: the (maximum) sequence length; nbh: sequences x query heads
@@ -48,7 +48,7 @@ struct FwdSmem {
 // reference).
 constexpr float RESCALE_SLACK = 8.0f;
 
-template <int D>
+template <int D, bool F32>
 __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
   constexpr int BM = FWD_BM, BN = FWD_BN;
   constexpr int DS = D / 16, DB = D / 32, KB = BN / 32, PC = BN / 16;
@@ -310,12 +310,12 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
   const float lt = halves_sum(lsum);
   if (qvalid) {
     const float inv = 1.f / lt;
-    bf16* op = p.O + (qbase + prow) * D + 4 * g2;
+    const size_t op = (qbase + prow) * D + 4 * g2;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        st_bf16x4(op + db * 32 + 8 * i, oacc[db][4 * i] * inv, oacc[db][4 * i + 1] * inv,
+        st_out4<F32>(p.O, op + db * 32 + 8 * i, oacc[db][4 * i] * inv, oacc[db][4 * i + 1] * inv,
                   oacc[db][4 * i + 2] * inv, oacc[db][4 * i + 3] * inv);
     if (g2 == 0) p.LSE[qbase + prow] = (m + log2f(lt)) * LN2;
   }
@@ -328,7 +328,7 @@ hipError_t launch_fwd_d(const Shape& s, const void* Q, const void* K, const void
   p.Q = static_cast<const bf16*>(Q);
   p.K = static_cast<const bf16*>(K);
   p.V = static_cast<const bf16*>(V);
-  p.O = static_cast<bf16*>(O);
+  p.O = O;
   p.LSE = LSE;
   p.seq = s.seq;
   p.L = s.L;
@@ -340,7 +340,8 @@ hipError_t launch_fwd_d(const Shape& s, const void* Q, const void* K, const void
   p.nbh = s.B * s.Hq;
   p.c = s.scale * LOG2E;
   const dim3 grid(2 * p.nQT * p.nbh);
-  hipExtLaunchKernelGGL(fwd_kernel<D>, grid, dim3(256), 0, st, ev.start, ev.stop, 0, p);
+  if (s.out32) hipExtLaunchKernelGGL((fwd_kernel<D, true>), grid, dim3(256), 0, st, ev.start, ev.stop, 0, p);
+  else hipExtLaunchKernelGGL((fwd_kernel<D, false>), grid, dim3(256), 0, st, ev.start, ev.stop, 0, p);
   return hipGetLastError();
 }
 

@@ -109,6 +109,7 @@ struct Shape {
   int G;                    // Hq / Hkv
   float scale;              // softmax scale (already resolved)
   SeqLayout seq;
+  bool out32;               // O, dQ, dK, dV are float32 arrays (bf16 results widened)
 };
 
 // Forward tiles: BM queries per workgroup (4 waves x 32), BN keys per step.
@@ -125,8 +126,16 @@ struct LaunchEvents {
   hipEvent_t start = nullptr, stop = nullptr;
 };
 
-hipError_t launch_cast_f32_to_bf16(const float* x, void* y, size_t n, hipStream_t st, LaunchEvents ev = {});
-hipError_t launch_cast_bf16_to_f32(const void* x, float* y, size_t n, hipStream_t st, LaunchEvents ev = {});
+// Rounds up to CAST_MAX float32 tensors to bf16 in one launch; every count a
+// multiple of 8, every pointer 16-byte aligned.
+constexpr int CAST_MAX = 5;
+struct CastList {
+  const void* src[CAST_MAX];
+  void* dst[CAST_MAX];
+  size_t n[CAST_MAX];
+  int count;
+};
+hipError_t launch_cast_f32_to_bf16(const CastList& c, hipStream_t st, LaunchEvents ev = {});
 
 hipError_t launch_fwd(const Shape& s, const void* Q, const void* K, const void* V,
                       void* O, float* LSE, hipStream_t st, LaunchEvents ev = {});

@@ -93,6 +93,21 @@ def check_groups(w, groups, label):
 
 # ------------------------------------------------------------------ configs
 
+# float32 tensors take the bf16 kernels with inputs rounded on the way in and
+# results widened on the way out, so on values that bf16 holds exactly the
+# outputs are the bf16 call's, widened: noisy and clean key tiles, ragged ends,
+# walks in two parts (the last shape) and in four.
+@pytest.mark.parametrize("B,Hq,Hkv,D,L,S", [(1, 1, 1, 64, 1, 4), (2, 4, 2, 128, 130, 4), (1, 3, 1, 64, 257, 5),
+                                            (8, 8, 8, 64, 300, 32)])
+def test_fp32_equals_widened_bf16(B, Hq, Hkv, D, L, S):
+    _say(f"[parity] fp32 B{B} H{Hq}/{Hkv} D{D} L{L} S{S}")
+    t16 = make_random_case(B, Hq, Hkv, D, L, S, seed=77 + L)
+    r16 = run_gpu(*t16, L, S)
+    r32 = run_gpu(*(t.float() for t in t16), L, S)
+    for a, b in zip(r16, r32):
+        assert b.dtype == torch.float32 and torch.equal(a.float(), b)
+
+
 def test_tiny_fp32_config():
     w = WORKLOADS["tiny"]
     q, k, v, do = make_inputs(w)
