@@ -13,6 +13,7 @@ earlier blocks; a clean query sees clean keys of its own and earlier blocks.
 from __future__ import annotations
 
 import ctypes
+import functools
 
 import numpy as np
 import torch
@@ -43,16 +44,35 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"bd_attn supports bfloat16 and float32 tensors, got {t.dtype}")
 
 
-def _ptr(t) -> ctypes.c_void_p:
-    return ctypes.c_void_p(t.data_ptr())
+# The binding's own time is most of a small call (one sequence's decoding step:
+# 19 us a call around 12 us of kernels), so pointers go to the library as plain
+# integers, sizes that depend on the shape alone are looked up once per shape,
+# and a tensor that passes all its checks is tested in one expression.
+
+_ptr = torch.Tensor.data_ptr
 
 
-def _stream(device: torch.device, stream):
-    s = torch.cuda.current_stream(device) if stream is None else stream
-    return s, ctypes.c_void_p(s.cuda_stream)
+def _stream_handle(device: torch.device, stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
+def _workspace(nbytes: int, device: torch.device, workspace):
+    """The caller's workspace or a new one, and its pointer and size (none for 0 bytes)."""
+    if workspace is not None:
+        return workspace, workspace.data_ptr(), workspace.numel()
+    if nbytes == 0:
+        return None, None, 0
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
+    return ws, ws.data_ptr(), nbytes
 
 
 def _check(name: str, t: torch.Tensor, shape, dtype, device):
+    if t.shape == shape and t.dtype is dtype and t.device == device and t.is_contiguous():
+        return
     if tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
     if t.dtype != dtype:
@@ -61,6 +81,12 @@ def _check(name: str, t: torch.Tensor, shape, dtype, device):
         raise ValueError(f"{name}: expected device {device}, got {t.device}")
     if not t.is_contiguous():
         raise ValueError(f"{name}: must be contiguous")
+
+
+@functools.lru_cache(maxsize=1024)
+def _size(name: str, *args) -> int:
+    """The library's size function `name` (a function of the shape alone)."""
+    return int(getattr(lib(), name)(*args))
 
 
 def _scale_arg(scale) -> float:
@@ -163,19 +189,19 @@ def bd_attn_fwd(q, k, v, L: int, S: int, scale=None, out=None, lse=None, workspa
     l_ = torch.empty((B, Hq, 2 * L), dtype=torch.float32, device=dev) if lse is None else lse
     _check("out", o, q.shape, dt, dev)
     _check("lse", l_, (B, Hq, 2 * L), torch.float32, dev)
-    nbytes = bd_attn_workspace_bytes(B, L, S, Hq, Hkv, D, code, 0)
-    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=dev) if workspace is None else workspace
-    s, sh = _stream(dev, stream)
+    nbytes = _size("bd_attn_workspace_bytes", B, L, S, Hq, Hkv, D, code, 0)
+    ws, wp, wn = _workspace(nbytes, dev, workspace)
+    sh = _stream_handle(dev, stream)
     args = (_ptr(q), _ptr(k), _ptr(v), B, L, S, Hq, Hkv, D, _scale_arg(scale), code,
-            _ptr(o), _ptr(l_), _ptr(ws), ws.numel(), sh)
+            _ptr(o), _ptr(l_), wp, wn, sh)
     if _marks:
         st = lib().bd_attn_fwd_marked(*args, *_marks_arg(_marks))
     else:
         st = lib().bd_attn_fwd(*args)
     if st:
         raise BdAttnError(st, "bd_attn_fwd")
-    if stream is not None and workspace is None:
-        ws.record_stream(s)
+    if stream is not None and workspace is None and ws is not None:
+        ws.record_stream(stream)
     return o, l_
 
 
@@ -192,19 +218,19 @@ def bd_attn_bwd(do, q, k, v, o, lse, L: int, S: int, scale=None, dq=None, dk=Non
     dq_ = torch.empty_like(q) if dq is None else dq
     dk_ = torch.empty_like(k) if dk is None else dk
     dv_ = torch.empty_like(v) if dv is None else dv
-    nbytes = bd_attn_workspace_bytes(B, L, S, Hq, Hkv, D, code, 1)
-    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=dev) if workspace is None else workspace
-    s, sh = _stream(dev, stream)
+    nbytes = _size("bd_attn_workspace_bytes", B, L, S, Hq, Hkv, D, code, 1)
+    ws, wp, wn = _workspace(nbytes, dev, workspace)
+    sh = _stream_handle(dev, stream)
     args = (_ptr(do), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), B, L, S, Hq, Hkv, D,
-            _scale_arg(scale), code, _ptr(dq_), _ptr(dk_), _ptr(dv_), _ptr(ws), ws.numel(), sh)
+            _scale_arg(scale), code, _ptr(dq_), _ptr(dk_), _ptr(dv_), wp, wn, sh)
     if _marks:
         st = lib().bd_attn_bwd_marked(*args, *_marks_arg(_marks))
     else:
         st = lib().bd_attn_bwd(*args)
     if st:
         raise BdAttnError(st, "bd_attn_bwd")
-    if stream is not None and workspace is None:
-        ws.record_stream(s)
+    if stream is not None and workspace is None and ws is not None:
+        ws.record_stream(stream)
     return dq_, dk_, dv_
 
 
@@ -223,7 +249,7 @@ def bd_attn_bwd_noalloc(do, q, k, v, o, lse, L: int, S: int, dq, dk, dv, scale=N
                          ("dk", dk, (B, Hkv, 2 * L, D)), ("dv", dv, (B, Hkv, 2 * L, D))):
         _check(name, t, shp, dt, dev)
     _check("lse", lse, (B, Hq, 2 * L), torch.float32, dev)
-    _, sh = _stream(dev, stream)
+    sh = _stream_handle(dev, stream)
     st = lib().bd_attn_bwd_noalloc(_ptr(do), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), B, L, S, Hq, Hkv, D,
                                    _scale_arg(scale), code, _ptr(dq), _ptr(dk), _ptr(dv), sh)
     if st:
@@ -289,15 +315,15 @@ def bd_attn_varlen_fwd(q, k, v, cu_seqlens, max_L: int, S: int, scale=None, out=
     l_ = torch.empty((Hq, 2 * T), dtype=torch.float32, device=dev) if lse is None else lse
     _check("out", o, q.shape, dt, dev)
     _check("lse", l_, (Hq, 2 * T), torch.float32, dev)
-    nbytes = bd_attn_varlen_workspace_bytes(n, T, max_L, S, Hq, Hkv, D, code, 0)
-    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=dev) if workspace is None else workspace
-    s, sh = _stream(dev, stream)
+    nbytes = _size("bd_attn_varlen_workspace_bytes", n, T, max_L, S, Hq, Hkv, D, code, 0)
+    ws, wp, wn = _workspace(nbytes, dev, workspace)
+    sh = _stream_handle(dev, stream)
     st = lib().bd_attn_varlen_fwd(_ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens), n, T, max_L, S, Hq, Hkv, D,
-                                  _scale_arg(scale), code, _ptr(o), _ptr(l_), _ptr(ws), ws.numel(), sh)
+                                  _scale_arg(scale), code, _ptr(o), _ptr(l_), wp, wn, sh)
     if st:
         raise BdAttnError(st, "bd_attn_varlen_fwd")
-    if stream is not None and workspace is None:
-        ws.record_stream(s)
+    if stream is not None and workspace is None and ws is not None:
+        ws.record_stream(stream)
     return o, l_
 
 
@@ -314,16 +340,16 @@ def bd_attn_varlen_bwd(do, q, k, v, o, lse, cu_seqlens, max_L: int, S: int, scal
     dq_ = torch.empty_like(q) if dq is None else dq
     dk_ = torch.empty_like(k) if dk is None else dk
     dv_ = torch.empty_like(v) if dv is None else dv
-    nbytes = bd_attn_varlen_workspace_bytes(n, T, max_L, S, Hq, Hkv, D, code, 1)
-    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=dev) if workspace is None else workspace
-    s, sh = _stream(dev, stream)
+    nbytes = _size("bd_attn_varlen_workspace_bytes", n, T, max_L, S, Hq, Hkv, D, code, 1)
+    ws, wp, wn = _workspace(nbytes, dev, workspace)
+    sh = _stream_handle(dev, stream)
     st = lib().bd_attn_varlen_bwd(_ptr(do), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(cu_seqlens), n,
                                   T, max_L, S, Hq, Hkv, D, _scale_arg(scale), code, _ptr(dq_), _ptr(dk_),
-                                  _ptr(dv_), _ptr(ws), ws.numel(), sh)
+                                  _ptr(dv_), wp, wn, sh)
     if st:
         raise BdAttnError(st, "bd_attn_varlen_bwd")
-    if stream is not None and workspace is None:
-        ws.record_stream(s)
+    if stream is not None and workspace is None and ws is not None:
+        ws.record_stream(stream)
     return dq_, dk_, dv_
 
 
@@ -374,16 +400,16 @@ def bd_attn_decode_fwd(q, k_cache, v_cache, k_new, v_new, cache_lens, scale=None
     l_ = torch.empty((B, Hq, S), dtype=torch.float32, device=dev) if lse is None else lse
     _check("out", o, q.shape, torch.bfloat16, dev)
     _check("lse", l_, (B, Hq, S), torch.float32, dev)
-    nbytes = bd_attn_decode_workspace_bytes(B, S, Hq, Hkv, D, C, BD_ATTN_BF16)
-    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=dev) if workspace is None else workspace
-    s, sh = _stream(dev, stream)
+    nbytes = _size("bd_attn_decode_workspace_bytes", B, S, Hq, Hkv, D, C, BD_ATTN_BF16)
+    ws, wp, wn = _workspace(nbytes, dev, workspace)
+    sh = _stream_handle(dev, stream)
     st = lib().bd_attn_decode_fwd(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_new), _ptr(v_new),
                                   _ptr(cache_lens), B, S, Hq, Hkv, D, C, _scale_arg(scale), BD_ATTN_BF16,
-                                  _ptr(o), _ptr(l_), _ptr(ws), ws.numel(), sh)
+                                  _ptr(o), _ptr(l_), wp, wn, sh)
     if st:
         raise BdAttnError(st, "bd_attn_decode_fwd")
-    if stream is not None and workspace is None:
-        ws.record_stream(s)
+    if stream is not None and workspace is None and ws is not None:
+        ws.record_stream(stream)
     return o, l_
 
 
@@ -426,16 +452,15 @@ def bd_lce_fwd(h, w, targets, lse=None, logp=None, workspace=None, stream=None, 
     lp = torch.empty(N, dtype=torch.float32, device=dev) if logp is None else logp
     _check("lse", l_, (N,), torch.float32, dev)
     _check("logp", lp, (N,), torch.float32, dev)
-    nbytes = bd_lce_workspace_bytes(N, V, Dm, 0)
-    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=dev) if workspace is None else workspace
-    s, sh = _stream(dev, stream)
-    kl = ctypes.c_void_p(None) if logits is None else _ptr(logits)
-    st = lib().bd_lce_fwd(_ptr(h), _ptr(w), _ptr(targets), N, V, Dm, BD_ATTN_BF16, _ptr(l_), _ptr(lp), kl, _ptr(ws),
-                          ws.numel(), sh)
+    nbytes = _size("bd_lce_workspace_bytes", N, V, Dm, BD_ATTN_BF16, 0)
+    ws, wp, wn = _workspace(nbytes, dev, workspace)
+    sh = _stream_handle(dev, stream)
+    kl = None if logits is None else _ptr(logits)
+    st = lib().bd_lce_fwd(_ptr(h), _ptr(w), _ptr(targets), N, V, Dm, BD_ATTN_BF16, _ptr(l_), _ptr(lp), kl, wp, wn, sh)
     if st:
         raise BdAttnError(st, "bd_lce_fwd")
-    if stream is not None and workspace is None:
-        ws.record_stream(s)
+    if stream is not None and workspace is None and ws is not None:
+        ws.record_stream(stream)
     return l_, lp
 
 
@@ -452,16 +477,16 @@ def bd_lce_bwd(h, w, targets, lse, dlogp, dh=None, dw=None, workspace=None, stre
     dw_ = torch.empty_like(w) if dw is None else dw
     _check("dh", dh_, (N, Dm), torch.bfloat16, dev)
     _check("dw", dw_, (V, Dm), torch.bfloat16, dev)
-    nbytes = bd_lce_workspace_bytes(N, V, Dm, 1)
-    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=dev) if workspace is None else workspace
-    s, sh = _stream(dev, stream)
-    kl = ctypes.c_void_p(None) if logits is None else _ptr(logits)
+    nbytes = _size("bd_lce_workspace_bytes", N, V, Dm, BD_ATTN_BF16, 1)
+    ws, wp, wn = _workspace(nbytes, dev, workspace)
+    sh = _stream_handle(dev, stream)
+    kl = None if logits is None else _ptr(logits)
     st = lib().bd_lce_bwd(_ptr(h), _ptr(w), _ptr(targets), _ptr(lse), _ptr(dlogp), kl, N, V, Dm, BD_ATTN_BF16,
-                          _ptr(dh_), _ptr(dw_), _ptr(ws), ws.numel(), sh)
+                          _ptr(dh_), _ptr(dw_), wp, wn, sh)
     if st:
         raise BdAttnError(st, "bd_lce_bwd")
-    if stream is not None and workspace is None:
-        ws.record_stream(s)
+    if stream is not None and workspace is None and ws is not None:
+        ws.record_stream(stream)
     return dh_, dw_
 
 
@@ -477,8 +502,8 @@ def bd_lce_objective(logp, weight, kind=BD_LCE_CE, logp_old=None, logp_ref=None,
             _check(name, t, (N,), torch.float32, dev)
     lo = torch.empty(N, dtype=torch.float32, device=dev) if loss is None else loss
     dl = torch.empty(N, dtype=torch.float32, device=dev) if dlogp is None else dlogp
-    opt = lambda t: ctypes.c_void_p(None) if t is None else _ptr(t)  # noqa: E731
-    _, sh = _stream(dev, stream)
+    opt = lambda t: None if t is None else _ptr(t)  # noqa: E731
+    sh = _stream_handle(dev, stream)
     st = lib().bd_lce_objective(_ptr(logp), opt(logp_old), opt(logp_ref), opt(adv), _ptr(weight), N, int(kind),
                                 float(eps), float(beta), _ptr(lo), _ptr(dl), sh)
     if st:
