@@ -34,9 +34,9 @@
 //   TW = 2, 4 (up to 64 rows, more): a workgroup is one team, whose waves share
 //     each tile, so a KV row is fetched once for up to 128 query rows; one
 //     barrier per tile.  24 sequences of 512..8192 tokens, 32 query and 8 KV
-//     heads of 128, S = 32 (128 rows per KV head): 93 us, 4.0 TB/s; with one
-//     wave per 32 rows, which fetched the cache four times, 203 us.  (Tiles of
-//     32 keys: 104 us; eight waves, half the keys of a tile each: 95 us.)
+//     heads of 128, S = 32 (128 rows per KV head, 370 MB): 93 us; with one wave
+//     per 32 rows, which fetched the cache four times, 203 us.  (Tiles of 32
+//     keys: 104 us; eight waves, half the keys of a tile each: 95 us.)
 // Per tile: S^T = K Q^T (a lane owns a query column, as in the forward pass),
 // P = exp2(c S - m) against a lazily moved reference max, O^T += V^T P^T with
 // V^T read through the transposing LDS read.
@@ -82,6 +82,13 @@ __device__ inline int dec_tiles(const DecParams& p, int len) {
 // same within 2% on one sequence of 1500 tokens), and no run is empty (T >= 1).
 constexpr int DEC_MIN_RUN = 2;
 __device__ inline int dec_runs(int runs, int T) { return imin(runs, cdiv(T, DEC_MIN_RUN)); }
+// Keys and values of more than the 256 MiB of the last-level cache are loaded
+// nontemporal: nothing of them survives to the next call, and without their
+// lines in L2 and the last-level cache the same bytes come faster (822 MB: 150
+// -> 132 us, 6.2 TB/s; 393 MB, whole call: 79 -> 71 us).  Smaller ones may still
+// be there from the last call, as when a block is denoised step by step (262
+// MB: 48 us, 51 nontemporal; 66 MB: 20, 22).
+constexpr size_t DEC_STREAM_BYTES = (size_t)288 << 20;
 // First tile of run gw (the runs cut T tiles into n near-equal pieces).
 __device__ inline int dec_run_start(int gw, int n, int T) { return (int)(((long long)gw * T) / n); }
 // First row of the partial slot of run gw for row group g of (sequence, KV head) bh.
@@ -148,6 +155,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
   const int excl = before + incl - csum;  // tiles per item of the sequences before c0
   const int T = total * I;                // checked on the host to fit in 31 bits
   const int n = dec_runs(p.runs, T);
+  const bool stream = (size_t)(total * p.Hkv) * (2 * Smem::TILE) > DEC_STREAM_BYTES;
   // Consecutive runs go to different workgroups: where fewer teams than the
   // grid holds take part, they are spread over the CUs.
   // the thread whose sequences hold a team's first tile records where it lies
@@ -182,7 +190,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
   pc.j = off - pc.r * pc.nt;
   const int S = p.S;
 
-  auto advance = [&](DecPos q) {
+  auto advance = [&](DecPos q) __attribute__((always_inline)) {
     if (++q.j == q.nt) {
       q.j = 0;
       if (++q.r == I) {
@@ -199,7 +207,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
   // rows of KV head r / ng (those rows are consecutive in Q, O and LSE).  A
   // lane past the last row takes the last row instead: its score column is
   // computed like the others (columns never mix) and never stored.
-  auto query_row = [&](DecPos q, bool& valid) {
+  auto query_row = [&](DecPos q, bool& valid) __attribute__((always_inline)) {
     const int hkv = q.r / p.ng, g = q.r - hkv * p.ng, rl = 32 * tw + l32, R = g * p.grows + rl;
     valid = R < p.G * S && (TW == 1 || rl < p.grows);
     return ((size_t)q.b * p.Hq + (size_t)hkv * p.G) * S + (R < p.G * S ? R : p.G * S - 1);
@@ -207,7 +215,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
   struct QRows {
     bf16x8 v[DS];
   };
-  auto load_q = [&](DecPos q) {
+  auto load_q = [&](DecPos q) __attribute__((always_inline)) {
     bool valid;
     const size_t row = query_row(q, valid);
     QRows r;
@@ -219,22 +227,24 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
   const TileCopy<D, KT, 64 * TW> copy(TW == 1 ? lane : tid);  // the team copies a whole tile
   constexpr int NI = decltype(copy)::NI;
   // copy K and V of the tile at q to dst, dst + TILE
-  auto issue = [&](DecPos q, char* dst) {
+  auto issue = [&](DecPos q, char* dst, auto streamed) __attribute__((always_inline)) {
     const size_t grp = (size_t)q.b * p.Hkv + q.r / p.ng;
     const int ntc = cdiv(q.len, KT);
     const bool cached = q.j < ntc;
     const int r0 = (cached ? q.j : q.j - ntc) * KT;
     const int left = (cached ? q.len : S) - r0;
     const size_t off2 = (cached ? grp * p.C : grp * S) * D + (size_t)r0 * D;
-    copy.issue_rows((cached ? p.Kc : p.Kn) + off2, left, dst);
-    copy.issue_rows((cached ? p.Vc : p.Vn) + off2, left, dst + Smem::TILE);
+    const bf16 *k = (cached ? p.Kc : p.Kn) + off2, *v = (cached ? p.Vc : p.Vn) + off2;
+    constexpr int POLICY = decltype(streamed)::value ? COPY_STREAM : 0;
+    copy.template issue_rows<POLICY>(k, left, dst);
+    copy.template issue_rows<POLICY>(v, left, dst + Smem::TILE);
   };
 
   const LdsOperands<D> ops(lane);
   QRows qreg, qnext;
   f32x16 oacc[DB];
   float m, lsum;
-  auto reset = [&]() {
+  auto reset = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -250,7 +260,8 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
 #pragma unroll
   for (int u = 0; u < NST - 1; ++u)
     if (x0 + u < x1) {
-      issue(pa, ring + u * 2 * Smem::TILE);
+      if (stream) issue(pa, ring + u * 2 * Smem::TILE, Flag<true>());
+      else issue(pa, ring + u * 2 * Smem::TILE, Flag<false>());
       pa = advance(pa);
     }
   if (TW > 1) {
@@ -261,7 +272,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
   int seg_j0 = pc.j;           // tile of the item this run's segment starts at
 
   // Write out the state of the current item's segment, which ends at tile pc.j.
-  auto flush = [&]() {
+  auto flush = [&]() __attribute__((always_inline)) {
     const int item = pc.b * I + pc.r;
     const bool ends = pc.j == pc.nt - 1;
     bool valid;
@@ -307,7 +318,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
   // The restrict qualifiers tell the compiler that the copy in flight does not
   // touch `cur`, so its reads need not wait for it.
   auto step = [&](const char* __restrict__ cur, char* __restrict__ nxt, DecPos pn, bool copies,
-                  bool new_item) __attribute__((always_inline)) {
+                  bool new_item, auto streamed) __attribute__((always_inline)) {
     compute_fence();  // the reads of the buffer about to be refilled are done
     if constexpr (TW == 1) {
       // Query rows of the next item (the tile at pn) are loaded a tile ahead,
@@ -315,7 +326,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
       // issue order.  (The query-row copy sits in both branches so that the
       // compiler's own wait for it counts the copy just issued on the first one.)
       if (copies) {
-        issue(pa, nxt);
+        issue(pa, nxt, streamed);
         wait_global_loads_but<(NST - 1) * 2 * NI>();  // the tile at pc has landed (this wave's own copy)
         if (new_item) qreg = qnext;
         if (pn.j == 0) qnext = load_q(pn);
@@ -327,7 +338,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
       if (copies) wait_global_loads_but<(NST - 2) * 2 * NI>();  // this wave's part of the tile at pc has landed
       else wait_global_loads();
       barrier_lds_only();  // ... every wave's; and all are done with `nxt`
-      if (copies) issue(pa, nxt);
+      if (copies) issue(pa, nxt, streamed);
       // A new item's query rows, waited for at once: were they still in flight
       // at the end of this branch, the compiler would wait for them, and so for
       // every copy in flight, in front of each tile's first product (121 instead
@@ -397,23 +408,28 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
 
   uint32_t bcur = 0;                           // ring offset of the tile at pc
   uint32_t bnxt = (NST - 1) * 2 * Smem::TILE;  // ring offset the copy NST - 1 ahead goes to
-  for (int x = x0; x < x1; ++x) {
-    const DecPos pn = advance(pc);
-    const bool more = x + 1 < x1, copies = x + NST - 1 < x1;
-    step(ring + bcur, ring + bnxt, pn, copies, x > x0 && pc.j == 0);
-    if (copies) pa = advance(pa);
-    bnxt = bcur;
-    bcur = bcur == (NST - 1) * 2 * Smem::TILE ? 0u : bcur + 2 * Smem::TILE;
-    if (!more || pn.j == 0) {
-      flush();
-      if (more) {  // the next tile starts the next item
-        reset();
-        item_start += pc.nt;
-        seg_j0 = 0;
+  // (the loop twice: a branch around the copies inside a step costs the teams 4%)
+  auto all_steps = [&](auto streamed) __attribute__((always_inline)) {
+    for (int x = x0; x < x1; ++x) {
+      const DecPos pn = advance(pc);
+      const bool more = x + 1 < x1, copies = x + NST - 1 < x1;
+      step(ring + bcur, ring + bnxt, pn, copies, x > x0 && pc.j == 0, streamed);
+      if (copies) pa = advance(pa);
+      bnxt = bcur;
+      bcur = bcur == (NST - 1) * 2 * Smem::TILE ? 0u : bcur + 2 * Smem::TILE;
+      if (!more || pn.j == 0) {
+        flush();
+        if (more) {  // the next tile starts the next item
+          reset();
+          item_start += pc.nt;
+          seg_j0 = 0;
+        }
       }
+      pc = pn;
     }
-    pc = pn;
-  }
+  };
+  if (stream) all_steps(Flag<true>());
+  else all_steps(Flag<false>());
 }
 
 // Merge the runs of each query row of an item held by several teams:

@@ -163,6 +163,8 @@ __device__ inline __amdgpu_buffer_rsrc_t make_buffer(const void* base, uint32_t 
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 
+constexpr int COPY_STREAM = 2;  // cache-policy bit: nontemporal, for data read once
+
 // Asynchronous copy of a tile of NR rows x D bf16 from a row-major array into
 // a swizzled LDS tile with buffer_load ... lds (16 bytes per lane; the LDS
 // address of lane i is M0 + 16*i).  Each wave instruction fills 1 KiB of the
@@ -202,17 +204,20 @@ struct TileCopy {
   __device__ static __amdgpu_buffer_rsrc_t rows(const bf16* arr, int nrows, int row0) {
     return make_buffer(arr + (size_t)row0 * D, (uint32_t)((nrows - row0) * D * 2));
   }
-  // Instruction u of the copy of the tile at the start of rsrc into dst.
+  // Instruction u of the copy of the tile at the start of rsrc into dst.  POLICY:
+  // cache-policy bits of the load (COPY_STREAM: nontemporal).
+  template <int POLICY = 0>
   __device__ void issue_one(__amdgpu_buffer_rsrc_t rsrc, char* dst, int u) const {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        rsrc, (__attribute__((address_space(3))) void*)(dst + (u * NW + wave) * 1024), 16, (int)boff[u], 0, 0, 0);
+        rsrc, (__attribute__((address_space(3))) void*)(dst + (u * NW + wave) * 1024), 16, (int)boff[u], 0, 0, POLICY);
   }
   // Copy the NR rows starting at `first` (of which `left` lie inside the
   // array; the rest read as zero) into the tile at dst.
+  template <int POLICY = 0>
   __device__ void issue_rows(const bf16* first, int left, char* dst) const {
     const __amdgpu_buffer_rsrc_t rsrc = make_buffer(first, (uint32_t)(left * D * 2));
 #pragma unroll
-    for (int u = 0; u < NI; ++u) issue_one(rsrc, dst, u);
+    for (int u = 0; u < NI; ++u) issue_one<POLICY>(rsrc, dst, u);
   }
   // Copy rows [row0, row0 + NR) of arr[nrows][D] into the tile at dst.
   __device__ void issue(const bf16* arr, int nrows, int row0, char* dst) const {

@@ -154,6 +154,23 @@ def test_decode_full_workload_sampled_rows():
         _check(_np(o[b:b + 1, h:h + 1]), _np(lse[b:b + 1, h:h + 1]), Or, LSEr, f"full b{b} h{h} len{n}")
 
 
+@pytest.mark.parametrize("Hq,S", [(16, 32), (32, 32)])
+def test_decode_streamed_teams_sampled_rows(Hq, S):
+    """More keys and values than the last-level cache holds (340 MB), so the
+    teams of two and of four waves load them nontemporal; sampled heads."""
+    B, Hkv, D, C = 40, 8, 128, 2080
+    lens = [C - 3 * b for b in range(B)]
+    q, kc, vc, kn, vn, cl = make_decode_inputs(B, Hq, Hkv, D, S, C, lens, seed=45, device="cuda")
+    o, lse = bd_attn_decode_fwd(q, kc, vc, kn, vn, cl)
+    torch.cuda.synchronize()
+    for b, h in [(0, 0), (B - 1, Hq - 1), (17, 5)]:
+        n, g = lens[b], h // (Hq // Hkv)
+        sl = lambda t, rows: t[b:b + 1, g:g + 1, :rows].double().cpu().numpy()  # noqa: E731
+        Or, LSEr = oracle.decode_forward(q[b:b + 1, h:h + 1].double().cpu().numpy(), sl(kc, n), sl(vc, n),
+                                         sl(kn, S), sl(vn, S), [n])
+        _check(_np(o[b:b + 1, h:h + 1]), _np(lse[b:b + 1, h:h + 1]), Or, LSEr, f"streamed b{b} h{h}")
+
+
 def test_decode_invalid_arguments():
     B, Hq, Hkv, D, S, C = 1, 4, 2, 64, 4, 64
     q, kc, vc, kn, vn, cl = (t.to(DEV) for t in make_decode_inputs(B, Hq, Hkv, D, S, C, [10], seed=44))
