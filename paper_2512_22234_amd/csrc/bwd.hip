@@ -889,11 +889,11 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqParams p) {
     kl.at(t, kh, j);
     const int k0 = j * BN;
     const PosWindow uw = kh == HALF_NOISY ? uw_n : uw_c;
-    issue(imin(t + 1, T - 1), nxt, nxt + 2 * TILE);
+    if (t + 1 < T) issue(t + 1, nxt, nxt + 2 * TILE);
 #pragma unroll 1
     for (int kb = 0; kb < KB; ++kb)  // (not unrolled: one block body in the loop)
       if (k0 + 32 * kb < uw.hi && k0 + 32 * kb + 32 > uw.lo) block_step(cur, cur + 2 * TILE, kh, k0, kb);
-    end_step();
+    if (t + 1 < T) end_step();  // (after the last tile nothing is in flight and nothing is read)
   }
 
   if (qvalid) {
