@@ -782,7 +782,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqParams p) {
   // One FULL key tile; restrict-qualified current and next buffers as in the
   // forward kernel, so the copy in flight does not make the compiler wait
   // before the reads of the current tile.  The copy of the next tile is
-  // spread between the MFMAs (the last step copies its own tile again).
+  // spread between the MFMAs (a walk ending here copies its last tile again).
   auto tile_step = [&](const char* __restrict__ kcur, const char* __restrict__ vcur, char* __restrict__ knxt,
                        char* __restrict__ vnxt, int t) __attribute__((always_inline)) {
     {

@@ -156,8 +156,8 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
   // kernel).  A CU accepts vector memory requests at a limited rate, so a
   // burst of copies at the top of the step would stall the wave; spread out,
   // each request issues while MFMAs run.
-  // The last step copies its own tile again (into the buffer nothing reads
-  // afterwards), which keeps the step straight-line code.
+  // (A walk that ends with a FULL tile copies that tile again, into the buffer
+  // nothing reads afterwards, which keeps the step straight-line code.)
   auto tile_step = [&](const char* __restrict__ kcur, const char* __restrict__ vcur, char* __restrict__ knxt,
                        char* __restrict__ vnxt, int t) __attribute__((always_inline)) {
     const int tn = imin(t + 1, T - 1);
