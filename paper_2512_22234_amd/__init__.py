@@ -83,10 +83,22 @@ def _check(name: str, t: torch.Tensor, shape, dtype, device):
         raise ValueError(f"{name}: must be contiguous")
 
 
-@functools.lru_cache(maxsize=1024)
 def _size(name: str, *args) -> int:
-    """The library's size function `name` (a function of the shape alone)."""
+    """The library's size function `name` (a function of the shape alone).
+
+    Only plain integers are looked up: a NumPy or torch scalar may change its
+    value in place, and need not be hashable."""
+    for a in args:
+        if type(a) is not int:
+            return _query_size(name, *args)
+    return _known_size(name, *args)
+
+
+def _query_size(name: str, *args) -> int:
     return int(getattr(lib(), name)(*args))
+
+
+_known_size = functools.lru_cache(maxsize=1024)(_query_size)
 
 
 def _scale_arg(scale) -> float:

@@ -8,6 +8,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_2512_22234_amd as bd
@@ -205,6 +206,25 @@ def test_varlen_workspace_bytes_follow_the_dkdv_split():
     assert f(6, 4096, 1701, 4, 32, 8, 128, 0, 1) == want(6, 4096, 1701, 32, 8, 128, 2)
     # few KV heads x tokens: four parts
     assert f(3, 600, 300, 4, 8, 2, 64, 0, 1) == want(3, 600, 300, 8, 2, 64, 4)
+
+
+def test_sizes_follow_integer_like_arguments():
+    """The calls take whatever ctypes takes as an integer: NumPy and torch
+    scalars as well as ints, at the value they hold at the time of the call."""
+    def size(L, S=4):
+        return bd._size("bd_attn_workspace_bytes", 2, L, S, 8, 2, 64, 0, 1)
+
+    want = {L: bd.bd_attn_workspace_bytes(2, L, 4, 8, 2, 64, 0, 1) for L in (300, 900)}
+    for L in (300, 900):
+        assert size(L) == want[L]
+        assert size(np.int64(L)) == size(np.array(L)) == size(torch.tensor(L)) == want[L]
+        assert size(L, S=np.array(4)) == want[L]
+    # the same object with another value
+    t, a = torch.tensor(300), np.array(300)
+    assert size(t) == size(a) == want[300]
+    t.fill_(900)
+    a.fill(900)
+    assert size(t) == size(a) == want[900]
 
 
 # Fake, never-dereferenced device addresses: every call below fails validation
