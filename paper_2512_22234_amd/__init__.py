@@ -83,22 +83,20 @@ def _check(name: str, t: torch.Tensor, shape, dtype, device):
         raise ValueError(f"{name}: must be contiguous")
 
 
-def _size(name: str, *args) -> int:
-    """The library's size function `name` (a function of the shape alone).
-
-    Only plain integers are looked up: a NumPy or torch scalar may change its
-    value in place, and need not be hashable."""
-    for a in args:
-        if type(a) is not int:
-            return _query_size(name, *args)
-    return _known_size(name, *args)
-
-
 def _query_size(name: str, *args) -> int:
+    """The library's size function `name` (a function of the shape alone)."""
     return int(getattr(lib(), name)(*args))
 
 
 _known_size = functools.lru_cache(maxsize=1024)(_query_size)
+
+
+def _size(a, b):
+    """The function that finds a call's size from the caller's own arguments a
+    and b (the rest come from tensor shapes): only plain integers are looked
+    up.  A NumPy or torch scalar may change its value in place, and need not be
+    hashable."""
+    return _known_size if type(a) is int and type(b) is int else _query_size
 
 
 def _scale_arg(scale) -> float:
@@ -201,7 +199,7 @@ def bd_attn_fwd(q, k, v, L: int, S: int, scale=None, out=None, lse=None, workspa
     l_ = torch.empty((B, Hq, 2 * L), dtype=torch.float32, device=dev) if lse is None else lse
     _check("out", o, q.shape, dt, dev)
     _check("lse", l_, (B, Hq, 2 * L), torch.float32, dev)
-    nbytes = _size("bd_attn_workspace_bytes", B, L, S, Hq, Hkv, D, code, 0)
+    nbytes = _size(L, S)("bd_attn_workspace_bytes", B, L, S, Hq, Hkv, D, code, 0)
     ws, wp, wn = _workspace(nbytes, dev, workspace)
     sh = _stream_handle(dev, stream)
     args = (_ptr(q), _ptr(k), _ptr(v), B, L, S, Hq, Hkv, D, _scale_arg(scale), code,
@@ -230,7 +228,7 @@ def bd_attn_bwd(do, q, k, v, o, lse, L: int, S: int, scale=None, dq=None, dk=Non
     dq_ = torch.empty_like(q) if dq is None else dq
     dk_ = torch.empty_like(k) if dk is None else dk
     dv_ = torch.empty_like(v) if dv is None else dv
-    nbytes = _size("bd_attn_workspace_bytes", B, L, S, Hq, Hkv, D, code, 1)
+    nbytes = _size(L, S)("bd_attn_workspace_bytes", B, L, S, Hq, Hkv, D, code, 1)
     ws, wp, wn = _workspace(nbytes, dev, workspace)
     sh = _stream_handle(dev, stream)
     args = (_ptr(do), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), B, L, S, Hq, Hkv, D,
@@ -327,7 +325,7 @@ def bd_attn_varlen_fwd(q, k, v, cu_seqlens, max_L: int, S: int, scale=None, out=
     l_ = torch.empty((Hq, 2 * T), dtype=torch.float32, device=dev) if lse is None else lse
     _check("out", o, q.shape, dt, dev)
     _check("lse", l_, (Hq, 2 * T), torch.float32, dev)
-    nbytes = _size("bd_attn_varlen_workspace_bytes", n, T, max_L, S, Hq, Hkv, D, code, 0)
+    nbytes = _size(max_L, S)("bd_attn_varlen_workspace_bytes", n, T, max_L, S, Hq, Hkv, D, code, 0)
     ws, wp, wn = _workspace(nbytes, dev, workspace)
     sh = _stream_handle(dev, stream)
     st = lib().bd_attn_varlen_fwd(_ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens), n, T, max_L, S, Hq, Hkv, D,
@@ -352,7 +350,7 @@ def bd_attn_varlen_bwd(do, q, k, v, o, lse, cu_seqlens, max_L: int, S: int, scal
     dq_ = torch.empty_like(q) if dq is None else dq
     dk_ = torch.empty_like(k) if dk is None else dk
     dv_ = torch.empty_like(v) if dv is None else dv
-    nbytes = _size("bd_attn_varlen_workspace_bytes", n, T, max_L, S, Hq, Hkv, D, code, 1)
+    nbytes = _size(max_L, S)("bd_attn_varlen_workspace_bytes", n, T, max_L, S, Hq, Hkv, D, code, 1)
     ws, wp, wn = _workspace(nbytes, dev, workspace)
     sh = _stream_handle(dev, stream)
     st = lib().bd_attn_varlen_bwd(_ptr(do), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(cu_seqlens), n,
@@ -412,7 +410,7 @@ def bd_attn_decode_fwd(q, k_cache, v_cache, k_new, v_new, cache_lens, scale=None
     l_ = torch.empty((B, Hq, S), dtype=torch.float32, device=dev) if lse is None else lse
     _check("out", o, q.shape, torch.bfloat16, dev)
     _check("lse", l_, (B, Hq, S), torch.float32, dev)
-    nbytes = _size("bd_attn_decode_workspace_bytes", B, S, Hq, Hkv, D, C, BD_ATTN_BF16)
+    nbytes = _known_size("bd_attn_decode_workspace_bytes", B, S, Hq, Hkv, D, C, BD_ATTN_BF16)
     ws, wp, wn = _workspace(nbytes, dev, workspace)
     sh = _stream_handle(dev, stream)
     st = lib().bd_attn_decode_fwd(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_new), _ptr(v_new),
@@ -464,7 +462,7 @@ def bd_lce_fwd(h, w, targets, lse=None, logp=None, workspace=None, stream=None, 
     lp = torch.empty(N, dtype=torch.float32, device=dev) if logp is None else logp
     _check("lse", l_, (N,), torch.float32, dev)
     _check("logp", lp, (N,), torch.float32, dev)
-    nbytes = _size("bd_lce_workspace_bytes", N, V, Dm, BD_ATTN_BF16, 0)
+    nbytes = _known_size("bd_lce_workspace_bytes", N, V, Dm, BD_ATTN_BF16, 0)
     ws, wp, wn = _workspace(nbytes, dev, workspace)
     sh = _stream_handle(dev, stream)
     kl = None if logits is None else _ptr(logits)
@@ -489,7 +487,7 @@ def bd_lce_bwd(h, w, targets, lse, dlogp, dh=None, dw=None, workspace=None, stre
     dw_ = torch.empty_like(w) if dw is None else dw
     _check("dh", dh_, (N, Dm), torch.bfloat16, dev)
     _check("dw", dw_, (V, Dm), torch.bfloat16, dev)
-    nbytes = _size("bd_lce_workspace_bytes", N, V, Dm, BD_ATTN_BF16, 1)
+    nbytes = _known_size("bd_lce_workspace_bytes", N, V, Dm, BD_ATTN_BF16, 1)
     ws, wp, wn = _workspace(nbytes, dev, workspace)
     sh = _stream_handle(dev, stream)
     kl = None if logits is None else _ptr(logits)

@@ -212,7 +212,7 @@ def test_sizes_follow_integer_like_arguments():
     """The calls take whatever ctypes takes as an integer: NumPy and torch
     scalars as well as ints, at the value they hold at the time of the call."""
     def size(L, S=4):
-        return bd._size("bd_attn_workspace_bytes", 2, L, S, 8, 2, 64, 0, 1)
+        return bd._size(L, S)("bd_attn_workspace_bytes", 2, L, S, 8, 2, 64, 0, 1)
 
     want = {L: bd.bd_attn_workspace_bytes(2, L, 4, 8, 2, 64, 0, 1) for L in (300, 900)}
     for L in (300, 900):
