@@ -55,9 +55,11 @@ _ptr = torch.Tensor.data_ptr
 def _stream_handle(device: torch.device, stream) -> int:
     if stream is not None:
         return stream.cuda_stream
-    if device.index is None:
+    # (a torch internal that saves building a Stream object, 1 us; not every build need have it)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or device.index is None:
         return torch.cuda.current_stream(device).cuda_stream
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    return raw(device.index)
 
 
 def _workspace(nbytes: int, device: torch.device, workspace):

@@ -227,6 +227,20 @@ def test_sizes_follow_integer_like_arguments():
     assert size(t) == size(a) == want[900]
 
 
+def test_stream_handle_without_torch_internals(monkeypatch):
+    """The current stream's handle is found through torch's public interface
+    where the internal function for it is missing."""
+    class Stream:
+        cuda_stream = 4321
+
+    seen = []
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device: seen.append(device) or Stream)
+    dev = torch.device("cuda", 1)
+    assert bd._stream_handle(dev, None) == 4321 and seen == [dev]
+    assert bd._stream_handle(dev, Stream) == 4321 and len(seen) == 1
+
+
 # Fake, never-dereferenced device addresses: every call below fails validation
 # and returns before any HIP call (the defaults use the float32 path so that
 # the workspace is non-empty and the workspace checks are exercised).
