@@ -118,7 +118,7 @@ int bd_attn_bwd(const void* dO, const void* Q, const void* K, const void* V,
  * the number of parts each clean key tile's dK/dV walk is split into: 4 when
  * B*Hkv*(L+128) <= 21845, else 2; 34.0 MiB for B=2, Hq=32, Hkv=8, D=128,
  * L=2048 and 68.0 MiB for B=1, L=8192 at the same heads; float32 inputs also
- * need bf16 copies of every tensor).  The call
+ * need bf16 copies of dO, Q, K, V and O).  The call
  * allocates and frees nothing; its first call on a GPU looks up that GPU's
  * copy of the array.  All calls on one GPU share the array and leave their
  * contents in it: calls whose work may overlap in time on one GPU (other

@@ -26,7 +26,7 @@ constexpr int kVersion = 100;  // 0.1.0
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-  size_t rs = 0, part = 0, pair = 0, q = 0, k = 0, v = 0, o = 0, dout = 0, dq = 0, dk = 0, dv = 0, total = 0;
+  size_t rs = 0, part = 0, pair = 0, q = 0, k = 0, v = 0, o = 0, dout = 0, total = 0;
 };
 
 bool shape_ok(int B, int L, int S, int Hq, int Hkv) {
@@ -52,18 +52,13 @@ Layout make_layout(const bd::Shape& s, int dtype, bool bwd) {
     off += align256(bd::dkdv_pair_ints(s.B, s.Hkv, s.L) * 4);
   }
   if (dtype == BD_ATTN_FP32) {
-    // bf16 copies of the inputs.  (The forward's o and dq, dk, dv are room that
-    // nothing uses: the kernels write float32 results themselves, and the size
-    // stays what callers have been told to allocate.)
+    // bf16 copies of the inputs (the kernels write float32 results themselves)
     w.q = off; off += align256(nq * 2);
     w.k = off; off += align256(nk * 2);
     w.v = off; off += align256(nk * 2);
-    w.o = off; off += align256(nq * 2);
     if (bwd) {
+      w.o = off; off += align256(nq * 2);
       w.dout = off; off += align256(nq * 2);
-      w.dq = off; off += align256(nq * 2);
-      w.dk = off; off += align256(nk * 2);
-      w.dv = off; off += align256(nk * 2);
     }
   }
   w.total = off;

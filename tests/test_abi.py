@@ -188,6 +188,20 @@ def test_workspace_bytes_follow_the_dkdv_split():
     assert f(2, 300, 4, 8, 2, 64, 0, 1) == want(2, 300, 8, 2, 64, 4)       # ragged last key tile
 
 
+def test_float32_workspace_holds_the_input_copies_only():
+    """A float32 call needs what the bf16 call needs and a bf16 copy of each
+    input (each rounded up to 256 bytes); its results are written in place."""
+    r256 = lambda x: -(-x // 256) * 256
+    for B, L, Hq, Hkv, D in ((1, 3, 1, 1, 64), (2, 300, 8, 2, 128), (1, 1024, 32, 8, 128)):
+        nq, nk = (r256(B * H * 2 * L * D * 2) for H in (Hq, Hkv))
+        f = lambda dtype, bwd: bd.bd_attn_workspace_bytes(B, L, 4, Hq, Hkv, D, dtype, bwd)
+        assert f(1, 0) - f(0, 0) == nq + 2 * nk
+        assert f(1, 1) - f(0, 1) == 3 * nq + 2 * nk
+        f = lambda dtype, bwd: bd.bd_attn_varlen_workspace_bytes(3, B * L, L, 4, Hq, Hkv, D, dtype, bwd)
+        assert f(1, 0) - f(0, 0) == nq + 2 * nk
+        assert f(1, 1) - f(0, 1) == 3 * nq + 2 * nk
+
+
 def test_varlen_workspace_bytes_follow_the_dkdv_split():
     """bf16 packed backward workspace = (lse2, delta) per query row + float32 sums
     of nsplit - 1 parts of the clean key tiles' walks (a bound on the key
@@ -442,6 +456,8 @@ def test_noalloc_scratch_size_matches_header():
     (dict(L=(1 << 22) + 1), 1),
     # workspace beyond the scratch array: rejected before any HIP call
     (dict(B=4, L=8192, Hq=32, Hkv=8, D=128), 5), (dict(B=1, L=8192, Hq=32, Hkv=8, D=128, dtype=1), 5),
+    # a float32 problem whose input copies fit: past the size check, refused for its null pointer
+    (dict(B=1, L=1024, Hq=32, Hkv=8, D=128, dtype=1, dO=0), 1),
     (dict(dO=0), 1), (dict(dV=0), 1), (dict(LSE=A + 5 * SZ + 2), 1), (dict(dK=A + 7 * SZ + 4), 1),
 ])
 def test_bwd_noalloc_validation(kw, status):
