@@ -46,6 +46,12 @@
 namespace bd {
 namespace {
 
+// The runs that hold an item: first and last, or last = -1 where the decode
+// kernel wrote the item directly.
+struct alignas(16) DecRuns {
+  int first, last;
+};
+
 struct DecParams {
   const bf16* Q;   // [B][Hq][S][D]
   const bf16* Kc;  // [B][Hkv][C][D]
@@ -55,7 +61,7 @@ struct DecParams {
   const int* cache_lens;  // [B], device
   bf16* O;                // [B][Hq][S][D]
   float* LSE;             // [B][Hq][S]
-  int4* desc;             // [item]: first run, last run (-1: the item was written directly), T
+  DecRuns* desc;          // [item]
   float* part;            // [row][D + 4]: unnormalised O, max (log2 units), sum
   int B, S, Hq, Hkv, G, C;
   int ng;     // row groups per (sequence, KV head)
@@ -291,7 +297,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
         }
         if (g2 == 0) p.LSE[qrow] = (m + __log2f(Lrow)) * LN2;
       }
-      if (lane == 0 && tw == 0) p.desc[item] = int4{0, -1, T, 0};
+      if (lane == 0 && tw == 0) p.desc[item] = DecRuns{0, -1};
       return;
     }
     if (valid) {
@@ -309,7 +315,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
     if (ends && lane == 0 && tw == 0) {
       // the runs holding this item: from the one holding its first tile to this one
       const int first = (int)((((long long)item_start + 1) * n - 1) / T);
-      p.desc[item] = int4{first, gw, T, 0};
+      p.desc[item] = DecRuns{first, gw};
     }
   };
 
@@ -453,7 +459,7 @@ __global__ __launch_bounds__(256) void dec_combine_kernel(DecParams p) {
   const int q4 = tid % TPR, part = (tid / TPR) % P;
   const size_t qrow = (size_t)blockIdx.x * RPW + tid / (TPR * P);  // row of Q: ((b * Hq + h) * S + s)
   const int GS = p.G * p.S;
-  int4 d = {0, -1, 0, 0};
+  DecRuns d = {0, -1};
   float M = -INFINITY, Lr = 0.f;
   f32x4 o = {0.f, 0.f, 0.f, 0.f};
   if (qrow < (size_t)p.B * p.Hkv * GS) {
@@ -462,7 +468,7 @@ __global__ __launch_bounds__(256) void dec_combine_kernel(DecParams p) {
     const int g = R / p.grows, r = R - g * p.grows;
     d = p.desc[bh * p.ng + g];  // (last run -1: written by the decode kernel itself)
 #pragma unroll 4
-    for (int gw = d.x + part; gw <= d.y; gw += P) {
+    for (int gw = d.first + part; gw <= d.last; gw += P) {
       const float* ps = p.part + (dec_slot_row(p, gw, bh, g) + r) * PST;
       const f32x4 ml = *reinterpret_cast<const f32x4*>(ps + D);
       const f32x4 v = *reinterpret_cast<const f32x4*>(ps + 4 * q4);
@@ -477,7 +483,7 @@ __global__ __launch_bounds__(256) void dec_combine_kernel(DecParams p) {
     so[tid] = o;
     sml[tid] = float2{M, Lr};
     __syncthreads();
-    if (part != 0 || d.y < 0) return;
+    if (part != 0 || d.last < 0) return;
     // (part 0 holds at least one run, so M is finite)
 #pragma unroll
     for (int u = 1; u < P; ++u) {
@@ -489,7 +495,7 @@ __global__ __launch_bounds__(256) void dec_combine_kernel(DecParams p) {
       o = o * a + v * c;
       M = Mn;
     }
-  } else if (d.y < 0) {
+  } else if (d.last < 0) {
     return;
   }
   const float inv = 1.f / Lr;
@@ -516,7 +522,7 @@ hipError_t launch_decode_d(const DecodeShape& s, const void* Q, const void* Kc, 
   p.cache_lens = cache_lens;
   p.O = static_cast<bf16*>(O);
   p.LSE = LSE;
-  p.desc = static_cast<int4*>(ws);
+  p.desc = static_cast<DecRuns*>(ws);
   p.part = reinterpret_cast<float*>(static_cast<char*>(ws) + decode_desc_bytes(s));
   p.B = s.B;
   p.S = s.S;

@@ -62,10 +62,6 @@ template <> __host__ __device__ inline int chunk_swizzle<128>(int r) {
 template <> __host__ __device__ inline int chunk_swizzle<64>(int r) {
   return (((r >> 1) & 3) << 1) | ((r >> 3) & 1);
 }
-// 64-byte rows (GEMM k-chunks of 32): four rows share a 256-byte bank cycle,
-// so 16 consecutive rows at one 16-byte column land on 16 distinct bank
-// groups when the chunk moves with row / 4.
-template <> __host__ __device__ inline int chunk_swizzle<32>(int r) { return (r >> 2) & 3; }
 // Element index of (row, col) in a swizzled tile; col % 8 stays in place.
 template <int D> __host__ __device__ inline int tile_idx(int row, int col) {
   return row * D + ((((col >> 3) ^ chunk_swizzle<D>(row)) << 3) | (col & 7));

@@ -207,7 +207,6 @@ inline size_t dkdv_pair_ints(int B, int Hkv, int L) {
 // waves, one wave per DEC_QT query rows of a group (DecodeGroups).
 constexpr int DEC_QT = 32, DEC_KT = 32, DEC_WAVES = 1024;
 
-
 struct DecodeShape {
   int B, S, Hq, Hkv, D;
   int C;  // cache capacity (rows per sequence and KV head)

@@ -44,7 +44,6 @@ namespace {
 
 constexpr int TB = 256;                // output tile (both sides)
 constexpr int BK = LCE_BK;             // k per chunk
-constexpr int KS = BK / 16;            // MFMA k steps per chunk
 constexpr uint32_t OPB = TB * BK * 2;  // bytes of one operand tile (32 KB)
 constexpr int RED_STRIDE = TB + 8;     // staging row stride (bf16) of the output tile: 528 bytes
 
