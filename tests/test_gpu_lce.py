@@ -67,15 +67,44 @@ def test_lce_matches_oracle(N, V, Dm):
     assert np.all(_np(logp)[unscored] == 0) and np.all(_np(dh)[unscored] == 0)
 
 
-# dH in parts of the vocabulary (few output tiles, at least 2048 vocabulary
-# rows a part): two parts, four over two ragged position tiles, nineteen; and just
-# too small a vocabulary for two.
-@pytest.mark.parametrize("N,V,Dm", [(5, 5000, 256), (300, 9000, 512), (33, 40001, 256), (70, 4095, 256)])
+# dH in parts of the vocabulary (few output tiles, at least 32 chunks of 64
+# vocabulary rows a part, the vocabulary rounded up to 256): two parts, four over
+# two ragged position tiles, nineteen; and on both sides of the smallest
+# vocabulary for two (4095 rows are 64 chunks, 3840 are 60).
+@pytest.mark.parametrize("N,V,Dm", [(5, 5000, 256), (300, 9000, 512), (33, 40001, 256), (70, 4095, 256),
+                                    (70, 3840, 256)])
 def test_lce_split_vocabulary_matches_oracle(N, V, Dm):
     test_lce_matches_oracle(N, V, Dm)
 
 
-@pytest.mark.parametrize("N,V,Dm", [(100, 1000, 256), (513, 2048, 768)])
+@pytest.mark.parametrize("N,V,Dm", [(2048, 8192, 256), (2047, 8190, 256), (2049, 8195, 256)])
+def test_lce_split_sums_stay_within_dw(N, V, Dm):
+    """The parts' float32 sums wait in dW, so 2 parts N <= V decides their number
+    here (128 chunks would allow four): at N = 2048 two parts fill dW exactly,
+    and at N = 2049 there is one part.  What lies on either side of dH and dW
+    stays as it was, and the gradients match the oracle."""
+    print(f"[lce] within dW N{N} V{V} Dm{Dm}", flush=True)
+    h, w, t = make_lce_inputs(N, V, Dm, seed=600 + N)
+    c = torch.randn(N, generator=torch.Generator().manual_seed(N), dtype=torch.float32)
+    hd, wd, td, cd = h.to(DEV), w.to(DEV), t.to(DEV), c.to(DEV)
+    guard = 8 * N * Dm  # as much as another two parts would take
+
+    def banded(rows):
+        flat = torch.full((2 * guard + rows * Dm,), 7.0, dtype=torch.bfloat16, device=DEV)
+        return flat, flat[guard:guard + rows * Dm].view(rows, Dm)
+
+    (fh, dh), (fw, dw) = banded(N), banded(V)
+    lse, _ = bd_lce_fwd(hd, wd, td)
+    bd_lce_bwd(hd, wd, td, lse, cd, dh=dh, dw=dw)
+    torch.cuda.synchronize()
+    for flat in (fh, fw):
+        assert bool((flat[:guard] == 7).all()) and bool((flat[-guard:] == 7).all())
+    dH_r, dW_r = oracle.lm_head_backward(h.double().numpy(), w.double().numpy(), t.numpy(), c.double().numpy())
+    assert _rel(_np(dh), dH_r) <= G_REL and _rel(_np(dw), dW_r) <= G_REL
+
+
+# (the last one with dH in four parts)
+@pytest.mark.parametrize("N,V,Dm", [(100, 1000, 256), (513, 2048, 768), (300, 9000, 512)])
 def test_lce_kept_logits_match_recompute(N, V, Dm):
     """The backward from kept logits agrees with the recomputing one and with
     the oracle; the kept logits themselves are the oracle's logits."""
