@@ -96,9 +96,9 @@ def check_groups(w, groups, label):
 # float32 tensors take the bf16 kernels with inputs rounded on the way in and
 # results widened on the way out, so on values that bf16 holds exactly the
 # outputs are the bf16 call's, widened: noisy and clean key tiles, ragged ends,
-# walks in two parts (the last shape) and in four.
+# walks in two parts (the last shape of each head size) and in four.
 @pytest.mark.parametrize("B,Hq,Hkv,D,L,S", [(1, 1, 1, 64, 1, 4), (2, 4, 2, 128, 130, 4), (1, 3, 1, 64, 257, 5),
-                                            (8, 8, 8, 64, 300, 32)])
+                                            (8, 8, 8, 64, 300, 32), (8, 8, 8, 128, 300, 4)])
 def test_fp32_equals_widened_bf16(B, Hq, Hkv, D, L, S):
     _say(f"[parity] fp32 B{B} H{Hq}/{Hkv} D{D} L{L} S{S}")
     t16 = make_random_case(B, Hq, Hkv, D, L, S, seed=77 + L)

@@ -65,6 +65,22 @@ def test_varlen_matches_oracle(lengths, Hq, Hkv, D, S, extra):
     assert max(errs["dq_rel"], errs["dk_rel"], errs["dv_rel"]) <= G_REL, errs
 
 
+@pytest.mark.parametrize("lengths,Hq,Hkv,D,S", [
+    ([300, 129, 0, 64, 1], 2, 1, 128, 8),                        # walks in four parts
+    ([37, 257, 130], 6, 2, 64, 5),
+    ([300, 37, 0, 129, 130] + [300] * 7, 8, 8, 128, 4),          # two parts
+    ([300, 37, 0, 129, 130] + [300] * 7, 8, 8, 64, 32),
+])
+def test_varlen_fp32_equals_widened_bf16(lengths, Hq, Hkv, D, S):
+    """float32 tensors holding bf16 values: the outputs are the bf16 call's, widened."""
+    print(f"[varlen] fp32 lengths={lengths} H{Hq}/{Hkv} D{D} S{S}", flush=True)
+    *t16, cu = make_varlen_inputs(lengths, Hq, Hkv, D, seed=240 + sum(lengths))
+    r16 = run_varlen(*t16, cu, max(lengths), S)
+    r32 = run_varlen(*(t.float() for t in t16), cu, max(lengths), S)
+    for a, b in zip(r16, r32):
+        assert b.dtype == torch.float32 and torch.equal(a.float(), b)
+
+
 def _pack(x):
     """[B, H, 2L, D] -> [H, 2BL, D]: sequence b at packed rows [2bL, 2(b+1)L)."""
     B, H, N, D = x.shape
