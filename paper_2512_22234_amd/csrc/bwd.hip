@@ -718,7 +718,6 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqParams p) {
 
   const int r = q0 + w * 32 + l32;
   const bool qvalid = r < q1;
-  const int qblock0 = qvalid ? (r / S) * S : 0;
   const int prow = qh * L + r;
   const size_t qrow = qrow0 + hq * hrows + prow;
 
@@ -834,6 +833,23 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqParams p) {
       pipeline_lds_reads<PC * DB, 4, 2>();
     }
   };
+  auto end_step = [&]() __attribute__((always_inline)) {
+    compute_fence();
+    wait_global_loads();
+    __syncthreads();
+  };
+  const int t_main = __builtin_amdgcn_readfirstlane(imin(T, fr.full_prefix(BN)));
+  for (int t = 0; t < t_main; ++t) {
+    char* cur = lds + (t & 1) * TILE;
+    char* nxt = lds + ((t + 1) & 1) * TILE;
+    tile_step(cur, cur + 2 * TILE, nxt, nxt + 2 * TILE, t);
+    end_step();
+  }
+  // (The row's block is computed here, where the diagonal steps need it; see
+  // the forward kernel.)
+  int rd = r;
+  asm volatile("" : "+v"(rd));
+  const int qblock0 = rd < q1 ? (rd / S) * S : 0;
   // One 32-key block kb of a diagonal key tile (the next tile's copy is
   // issued by the caller).
   auto block_step = [&](const char* __restrict__ kcur, const char* __restrict__ vcur, int kh, int k0, int kb)
@@ -851,7 +867,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqParams p) {
     }
     pipeline_lds_reads<2 * DS, 4, 1>();
     // dS = P (dP - delta) on the visible pairs, 0 elsewhere
-    const PosWindow win = keys_visible_from(qh, kh, qblock0, L, S, qvalid);
+    const PosWindow win = keys_visible_from(qh, kh, qblock0, L, S, rd < q1);
     const unsigned span = (unsigned)(win.hi - win.lo);
     const int rel = k0 + 32 * kb + 4 * g2 - win.lo;
 #pragma unroll
@@ -870,31 +886,24 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqParams p) {
     for (int db = 0; db < DB; ++db)
       dqacc[db] = mfma32(lds_tr<D>(kcur, ops.tr_rel0, ops.tr_rel1, 2 * kb + 1, db), d1, dqacc[db]);
   };
-  auto end_step = [&]() __attribute__((always_inline)) {
-    compute_fence();
-    wait_global_loads();
-    __syncthreads();
-  };
-  const int t_main = __builtin_amdgcn_readfirstlane(imin(T, fr.full_prefix(BN)));
-  for (int t = 0; t < t_main; ++t) {
-    char* cur = lds + (t & 1) * TILE;
-    char* nxt = lds + ((t + 1) & 1) * TILE;
-    tile_step(cur, cur + 2 * TILE, nxt, nxt + 2 * TILE, t);
-    end_step();
-  }
-  for (int t = t_main; t < T; ++t) {
+  auto diagonal_step = [&](int t, auto last) __attribute__((always_inline)) {
     char* cur = lds + (t & 1) * TILE;
     char* nxt = lds + ((t + 1) & 1) * TILE;
     int kh, j;
     kl.at(t, kh, j);
     const int k0 = j * BN;
     const PosWindow uw = kh == HALF_NOISY ? uw_n : uw_c;
-    if (t + 1 < T) issue(t + 1, nxt, nxt + 2 * TILE);
+    if constexpr (!decltype(last)::value) issue(t + 1, nxt, nxt + 2 * TILE);
 #pragma unroll 1
     for (int kb = 0; kb < KB; ++kb)  // (not unrolled: one block body in the loop)
       if (k0 + 32 * kb < uw.hi && k0 + 32 * kb + 32 > uw.lo) block_step(cur, cur + 2 * TILE, kh, k0, kb);
-    if (t + 1 < T) end_step();  // (after the last tile nothing is in flight and nothing is read)
-  }
+    if constexpr (!decltype(last)::value) end_step();
+  };
+  // The last step is a copy of its own, as in the forward kernel (8 heads of
+  // 128, L = 5342: 202.9 us with a last step like the others, 207.2 with tests
+  // around the copies and the wait, 199.4 so).
+  for (int t = t_main; t < T - 1; ++t) diagonal_step(t, Flag<false>());
+  if (t_main < T) diagonal_step(T - 1, Flag<true>());
 
   if (qvalid) {
     const size_t dqp = qrow * D + 4 * g2;

@@ -83,7 +83,6 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
 
   const int r = q0 + w * 32 + l32;  // this lane's query row (local to its half)
   const bool qvalid = r < q1;
-  const int qblock0 = qvalid ? (r / S) * S : 0;
   const int prow = qh * L + r;
 
   const KeyTileList kl = key_tiles_for_query_tile(qh, qi, L, S, BM, BN);
@@ -130,11 +129,8 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
   __syncthreads();
 
   // Per-step bookkeeping is a few scalar instructions: the FULL test is two
-  // comparisons against per-workgroup bounds and the visibility windows of
-  // both key halves are computed once.
+  // comparisons against per-workgroup bounds.
   const FullRange fr = full_range_vs_query_tile(qh, q0, q1, L, S, BM);
-  const PosWindow win_n = keys_visible_from(qh, HALF_NOISY, qblock0, L, S, qvalid);
-  const PosWindow win_c = keys_visible_from(qh, HALF_CLEAN, qblock0, L, S, qvalid);
   // The keys any row of this wave can see, per half (a wave-uniform union of
   // the rows' windows): on the diagonal tiles a 32-key block outside it is
   // skipped by this wave, MFMAs and softmax alike (its probabilities would all
@@ -218,6 +214,39 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
       pipeline_lds_reads<PC * DB, 4, 2>();  // V^T operand reads (two per MFMA) four MFMAs ahead
     }
   };
+  auto step_buffers = [&](int t, char*& cur, char*& nxt) __attribute__((always_inline)) {
+    cur = lds + (t & 1) * TILE;
+    nxt = lds + ((t + 1) & 1) * TILE;
+  };
+  auto end_step = [&]() __attribute__((always_inline)) {
+    compute_fence();
+    wait_global_loads();  // this wave's part of the next tile has landed in LDS
+    __syncthreads();      // ... for every wave, and every wave is done with this buffer
+  };
+  // The walk starts with the key tiles that are FULL for the whole query tile
+  // (clean keys of earlier blocks); one loop with a single step body runs
+  // them.  The remaining few tiles (the diagonal ones) run in a second loop
+  // whose steps skip, per wave, the 32-key blocks none of its rows sees.
+  // Keeping the two apart keeps the register assignment of the main loop
+  // free of the copies that merging several step bodies in one loop costs.
+  const int t_main = __builtin_amdgcn_readfirstlane(imin(T, fr.full_prefix(BN)));
+  for (int t = 0; t < t_main; ++t) {
+    char *cur, *nxt;
+    step_buffers(t, cur, nxt);
+    tile_step(cur, cur + 2 * TILE, nxt, nxt + 2 * TILE, t);
+    end_step();
+  }
+  // What only the diagonal steps need is computed here: the windows of this
+  // lane's row (the empty asm hides that rd is r, or they would be computed, and
+  // held, ahead of the main loop).  At D = 64 those registers are the ones with
+  // which the main loop reads its operands ahead of the MFMAs: with the windows
+  // held, the compiler dropped that order in a variant of this kernel (one head,
+  // L = 8192: 88.5 -> 103 us).
+  int rd = r;
+  asm volatile("" : "+v"(rd));
+  const int qblock0 = rd < q1 ? (rd / S) * S : 0;
+  const PosWindow win_n = keys_visible_from(qh, HALF_NOISY, qblock0, L, S, rd < q1);
+  const PosWindow win_c = keys_visible_from(qh, HALF_CLEAN, qblock0, L, S, rd < q1);
   // One 32-key block kb of a key tile, for the diagonal tiles: the same
   // arithmetic as a tile step restricted to those keys (masked by the window).
   // The next tile's copy is issued by the caller.
@@ -267,29 +296,7 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
     for (int db = 0; db < DB; ++db)
       oacc[db] = mfma32(lds_tr<D>(vcur, ops.tr_rel0, ops.tr_rel1, 2 * kb + 1, db), p1, oacc[db]);
   };
-  auto step_buffers = [&](int t, char*& cur, char*& nxt) __attribute__((always_inline)) {
-    cur = lds + (t & 1) * TILE;
-    nxt = lds + ((t + 1) & 1) * TILE;
-  };
-  auto end_step = [&]() __attribute__((always_inline)) {
-    compute_fence();
-    wait_global_loads();  // this wave's part of the next tile has landed in LDS
-    __syncthreads();      // ... for every wave, and every wave is done with this buffer
-  };
-  // The walk starts with the key tiles that are FULL for the whole query tile
-  // (clean keys of earlier blocks); one loop with a single step body runs
-  // them.  The remaining few tiles (the diagonal ones) run in a second loop
-  // whose steps skip, per wave, the 32-key blocks none of its rows sees.
-  // Keeping the two apart keeps the register assignment of the main loop
-  // free of the copies that merging several step bodies in one loop costs.
-  const int t_main = __builtin_amdgcn_readfirstlane(imin(T, fr.full_prefix(BN)));
-  for (int t = 0; t < t_main; ++t) {
-    char *cur, *nxt;
-    step_buffers(t, cur, nxt);
-    tile_step(cur, cur + 2 * TILE, nxt, nxt + 2 * TILE, t);
-    end_step();
-  }
-  for (int t = t_main; t < T; ++t) {
+  auto diagonal_step = [&](int t, auto last) __attribute__((always_inline)) {
     char *cur, *nxt;
     step_buffers(t, cur, nxt);
     int kh, j;
@@ -298,15 +305,23 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdParams p) {
     // (EMPTY tiles are never visited; were one visited, the window test of
     // PARTIAL tiles would mask all of it)
     const PosWindow uw = kh == HALF_NOISY ? uw_n : uw_c;
-    if (t + 1 < T) {
+    if constexpr (!decltype(last)::value) {
       issue(t + 1, false, nxt);
       issue(t + 1, true, nxt + 2 * TILE);
     }
 #pragma unroll 1
     for (int kb = 0; kb < KB; ++kb)  // (not unrolled: one block body in the loop)
       if (k0 + 32 * kb < uw.hi && k0 + 32 * kb + 32 > uw.lo) block_step(cur, cur + 2 * TILE, kh, k0, kb);
-    if (t + 1 < T) end_step();  // (after the last tile nothing is in flight and nothing is read)
-  }
+    if constexpr (!decltype(last)::value) end_step();
+  };
+  // The last step is a copy of its own, with nothing left to copy or to wait
+  // for.  (Tests around the copies and the wait in one shared body lengthen
+  // every step, which shows where a short last query tile, none of whose key
+  // tiles is FULL, walks all of them here.  8 heads of 128, L = 5342: 150.4 us
+  // with a last step like the others, 153.5 with the tests, 147.9 so; 32 heads,
+  // two sequences of 2048: 148.8, 146.3, 144.9.)
+  for (int t = t_main; t < T - 1; ++t) diagonal_step(t, Flag<false>());
+  if (t_main < T) diagonal_step(T - 1, Flag<true>());
 
   const float lt = halves_sum(lsum);
   if (qvalid) {

@@ -8,7 +8,10 @@ compiler's output shows:
     launch fails;
   * the forward and dQ kernels are written for two 256-thread workgroups per
     CU (same limit), and the dK/dV kernel's LDS must fit one CU's 160 KiB;
-  * no kernel may spill to scratch memory (a silent, large slowdown).
+  * no kernel may spill to scratch memory (a silent, large slowdown);
+  * the main loops of the forward and dQ kernels read their LDS operands ahead
+    of the MFMAs (a compiler that drops the requested order does so silently),
+    and their diagonal steps copy the next tile without a test.
 
 Each source is compiled to device assembly with the library's own flags and
 the kernel metadata is checked, so a change that breaks a budget fails here
@@ -47,19 +50,25 @@ def _metadata(asm: str) -> dict:
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
+def assembly(tmp_path_factory):
+    """Source name -> device assembly."""
     if not Path(HIPCC).exists():
         pytest.skip("hipcc not available")
     from paper_2512_22234_amd.build import compile_flags
-    meta = {}
+    texts = {}
     for src in ("fwd.hip", "bwd.hip"):
         out = tmp_path_factory.mktemp("isa") / (src + ".s")
         flags = [f for f in compile_flags(src) if f != "-fPIC"]
         cmd = [HIPCC, *flags, f"-I{CSRC}", "--cuda-device-only", "-S", "-o", str(out), str(CSRC / src)]
         r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
         assert r.returncode == 0, r.stderr[-2000:]
-        meta.update(_metadata(out.read_text()))
-    return meta
+        texts[src] = out.read_text()
+    return texts
+
+
+@pytest.fixture(scope="module")
+def kernels(assembly):
+    return {k: v for text in assembly.values() for k, v in _metadata(text).items()}
 
 
 def _find(meta, part):
@@ -88,6 +97,48 @@ def test_two_waves_per_simd_fit(kernels, part):
 def test_dkdv_lds_fits_one_cu(kernels):
     for name, f in _find(kernels, "dkdv_kernel").items():
         assert 0 < f["group_segment_fixed_size"] <= LDS_PER_CU, (name, f)
+
+
+def _blocks(text, part):
+    """Basic blocks (as lists of instructions) of every kernel whose name holds `part`."""
+    found = 0
+    for kernel in re.split(r"\n(?=_Z\S+:)", text):
+        if part not in kernel.split(":", 1)[0]:
+            continue
+        found += 1
+        for block in re.split(r"\n(?=\.LBB\S+:)", kernel):
+            yield [line.strip() for line in block.split("\n")[1:] if line.startswith("\t")]
+    assert found, part
+
+
+@pytest.mark.parametrize("src,part", [("fwd.hip", "fwd_kernelILi128"), ("fwd.hip", "fwd_kernelILi64"),
+                                      ("bwd.hip", "dq_kernelILi128"), ("bwd.hip", "dq_kernelILi64")])
+def test_main_loops_read_operands_ahead(assembly, src, part):
+    """Blocks that multiply without a wait for LDS in between let each MFMA wait
+    for its own operands while later reads are in flight: lgkmcnt(0) only at the
+    end of a run of MFMAs."""
+    loops = 0
+    for block in _blocks(assembly[src], part):
+        mfmas = sum("v_mfma" in x for x in block)
+        barrier = any("s_barrier" in x for x in block)
+        copies = any("buffer_load" in x for x in block)
+        if mfmas < 8 or not (barrier or copies):  # the main loop's blocks hold the step's copies or its end
+            continue
+        loops += 1
+        drained = sum("v_mfma" in y and "lgkmcnt(0)" in x for x, y in zip(block, block[1:]))
+        assert drained <= 2, (part, drained, mfmas)
+    assert loops >= 2, loops  # bf16 and float32 results
+
+
+@pytest.mark.parametrize("src,part", [("fwd.hip", "fwd_kernelILi128"), ("fwd.hip", "fwd_kernelILi64"),
+                                      ("bwd.hip", "dq_kernelILi128"), ("bwd.hip", "dq_kernelILi64")])
+def test_step_copies_are_unconditional(assembly, src, part):
+    """Only the prologue's copies stand behind a test (is there a key tile at all?)."""
+    tested = 0
+    for block in _blocks(assembly[src], part):
+        first = next((i for i, x in enumerate(block) if "buffer_load" in x), None)
+        tested += first is not None and any(x.startswith("s_cbranch") for x in block[:first])
+    assert tested <= 2, tested  # one per kernel: bf16 and float32 results
 
 
 def test_metadata_parser():
