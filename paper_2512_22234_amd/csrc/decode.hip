@@ -88,12 +88,18 @@ __device__ inline int dec_tiles(const DecParams& p, int len) {
 // same within 2% on one sequence of 1500 tokens), and no run is empty (T >= 1).
 constexpr int DEC_MIN_RUN = 2;
 __device__ inline int dec_runs(int runs, int T) { return imin(runs, cdiv(T, DEC_MIN_RUN)); }
-// Keys and values of more than the 256 MiB of the last-level cache are loaded
-// nontemporal: nothing of them survives to the next call, and without their
-// lines in L2 and the last-level cache the same bytes come faster (822 MB: 150
-// -> 132 us, 6.2 TB/s; 393 MB, whole call: 79 -> 71 us).  Smaller ones may still
-// be there from the last call, as when a block is denoised step by step (262
-// MB: 48 us, 51 nontemporal; 66 MB: 20, 22).
+// Keys and values of more than 288 MiB, beyond the 256 MiB of the last-level
+// cache, are loaded nontemporal: nothing of them survives to the next call, and
+// without their lines in L2 and the last-level cache the same bytes come faster
+// (822 MB: 150 -> 132 us, 6.2 TB/s).  Smaller ones may still be there from the
+// last call, as when a block is denoised step by step.  The line lies where both
+// are the same (64 sequences, S = 4, default and nontemporal: 264 MiB 49.9 and
+// 50.8 us, 288 MiB 52.4 and 53.9, 296 MiB 56.1 and 56.0, 312 MiB 59.9 and 58.1,
+// 336 MiB 68.8 and 61.1).  It holds for rows that a call reads more than once as
+// well, by the teams of a KV head's row groups: they run at about the same time
+// (256 query rows per KV head: 271 MiB 125 and 131 us, 337 MiB 157 and 156, 412
+// MiB 189 and 186, 768 MiB 334 and 324; 512 rows, 375 MiB, the other way round:
+// 312 and 316).
 constexpr size_t DEC_STREAM_BYTES = (size_t)288 << 20;
 // First tile of run gw (the runs cut T tiles into n near-equal pieces).
 __device__ inline int dec_run_start(int gw, int n, int T) { return (int)(((long long)gw * T) / n); }
@@ -134,7 +140,8 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g2 = lane >> 5;
   const int tm = TW == 1 ? w : 0, tw = TW == 1 ? 0 : w;  // team of the workgroup, wave of the team
-  const int I = p.Hkv * p.ng;                            // items per sequence
+  const int ng = TW < 4 ? 1 : p.ng;                      // (decode_groups: smaller teams hold all rows of a KV head)
+  const int I = p.Hkv * ng;                              // items per sequence
 
   // ---- prologue: T, and the position of each team's first tile ----
   // thread t sums the tiles per item of sequences [t*cpt, (t+1)*cpt)
@@ -209,12 +216,23 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
     }
     return q;
   };
+  // The kernel's arguments, read again.  Those needed once per item do not fit
+  // the scalar registers beside what the tile loop itself keeps there: held over
+  // the loop they went to vector lanes and a private segment.  (A team of four
+  // has no room for those of load_q either; one wave is 2% slower with them
+  // read again in front of each item: 8 sequences of up to 4096, S = 16, 23.8 us
+  // and 24.4.)
+  auto arguments = [&]() __attribute__((always_inline)) -> DecParams {
+    auto* a = (const __attribute__((address_space(4))) DecParams*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    return *(const DecParams*)a;
+  };
   // this lane's query row of item (b, r): row g*grows + 32*tw + l32 of the G*S
   // rows of KV head r / ng (those rows are consecutive in Q, O and LSE).  A
   // lane past the last row takes the last row instead: its score column is
   // computed like the others (columns never mix) and never stored.
-  auto query_row = [&](DecPos q, bool& valid) __attribute__((always_inline)) {
-    const int hkv = q.r / p.ng, g = q.r - hkv * p.ng, rl = 32 * tw + l32, R = g * p.grows + rl;
+  auto query_row = [&](const DecParams& p, DecPos q, bool& valid) __attribute__((always_inline)) {
+    const int hkv = q.r / ng, g = q.r - hkv * ng, rl = 32 * tw + l32, R = g * p.grows + rl;
     valid = R < p.G * S && (TW == 1 || rl < p.grows);
     return ((size_t)q.b * p.Hq + (size_t)hkv * p.G) * S + (R < p.G * S ? R : p.G * S - 1);
   };
@@ -222,11 +240,12 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
     bf16x8 v[DS];
   };
   auto load_q = [&](DecPos q) __attribute__((always_inline)) {
+    const DecParams a = TW == 4 ? arguments() : p;
     bool valid;
-    const size_t row = query_row(q, valid);
+    const size_t row = query_row(a, q, valid);
     QRows r;
 #pragma unroll
-    for (int s = 0; s < DS; ++s) r.v[s] = *reinterpret_cast<const bf16x8*>(p.Q + row * D + 16 * s + 8 * g2);
+    for (int s = 0; s < DS; ++s) r.v[s] = *reinterpret_cast<const bf16x8*>(a.Q + row * D + 16 * s + 8 * g2);
     return r;
   };
 
@@ -234,7 +253,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
   constexpr int NI = decltype(copy)::NI;
   // copy K and V of the tile at q to dst, dst + TILE
   auto issue = [&](DecPos q, char* dst, auto streamed) __attribute__((always_inline)) {
-    const size_t grp = (size_t)q.b * p.Hkv + q.r / p.ng;
+    const size_t grp = (size_t)q.b * p.Hkv + q.r / ng;
     const int ntc = cdiv(q.len, KT);
     const bool cached = q.j < ntc;
     const int r0 = (cached ? q.j : q.j - ntc) * KT;
@@ -246,196 +265,197 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
     copy.template issue_rows<POLICY>(v, left, dst + Smem::TILE);
   };
 
-  const LdsOperands<D> ops(lane);
-  QRows qreg, qnext;
-  f32x16 oacc[DB];
-  float m, lsum;
-  auto reset = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) oacc[db][e] = 0.f;
-    m = -INFINITY;
-    lsum = 0.f;
-  };
-  reset();
-  char* const ring = sm.buf[tm];
-  if (TW == 1) qreg = load_q(pc);
-  // the first NST - 1 tiles (those this run has); pa: the next tile to copy
-  DecPos pa = pc;
-#pragma unroll
-  for (int u = 0; u < NST - 1; ++u)
-    if (x0 + u < x1) {
-      if (stream) issue(pa, ring + u * 2 * Smem::TILE, Flag<true>());
-      else issue(pa, ring + u * 2 * Smem::TILE, Flag<false>());
-      pa = advance(pa);
-    }
-  if (TW > 1) {
-    qreg = load_q(pc);
-    wait_global_loads();
-  }
-  int item_start = x0 - pc.j;  // flat index of the current item's first tile
-  int seg_j0 = pc.j;           // tile of the item this run's segment starts at
-
-  // Write out the state of the current item's segment, which ends at tile pc.j.
-  auto flush = [&]() __attribute__((always_inline)) {
-    const int item = pc.b * I + pc.r;
-    const bool ends = pc.j == pc.nt - 1;
-    bool valid;
-    const size_t qrow = query_row(pc, valid);
-    const float Lrow = halves_sum(lsum);
-    if (seg_j0 == 0 && ends) {
-      if (valid) {
-        const float inv = 1.f / Lrow;
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          bf16* op = p.O + qrow * D + 32 * db + 4 * g2;
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            st_bf16x4(op + 8 * i, oacc[db][4 * i] * inv, oacc[db][4 * i + 1] * inv, oacc[db][4 * i + 2] * inv,
-                      oacc[db][4 * i + 3] * inv);
-        }
-        if (g2 == 0) p.LSE[qrow] = (m + __log2f(Lrow)) * LN2;
-      }
-      if (lane == 0 && tw == 0) p.desc[item] = DecRuns{0, -1};
-      return;
-    }
-    if (valid) {
-      const int hkv = pc.r / p.ng;
-      float* pr = p.part + (dec_slot_row(p, gw, (size_t)pc.b * p.Hkv + hkv, pc.r - hkv * p.ng) + 32 * tw + l32) * PST;
+  // The whole run, with or without the streaming hint on its copies.  (Twice in
+  // the code: a branch around the copies inside a step costs the teams 4%.  All
+  // state is the run's own: kept outside, that of the second copy would be held
+  // in registers through the first one's loop.)
+  auto run = [&](auto streamed) __attribute__((always_inline)) {
+    const LdsOperands<D> ops(lane);
+    QRows qreg, qnext;
+    f32x16 oacc[DB];
+    float m, lsum;
+    auto reset = [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const f32x4 v = {oacc[db][4 * i], oacc[db][4 * i + 1], oacc[db][4 * i + 2], oacc[db][4 * i + 3]};
-          *reinterpret_cast<f32x4*>(pr + 32 * db + 8 * i + 4 * g2) = v;
+        for (int e = 0; e < 16; ++e) oacc[db][e] = 0.f;
+      m = -INFINITY;
+      lsum = 0.f;
+    };
+    reset();
+    char* const ring = sm.buf[tm];
+    if (TW == 1) qreg = load_q(pc);
+    // the first NST - 1 tiles (those this run has); pa: the next tile to copy
+    DecPos pa = pc;
+#pragma unroll
+    for (int u = 0; u < NST - 1; ++u)
+      if (x0 + u < x1) {
+        issue(pa, ring + u * 2 * Smem::TILE, streamed);
+        pa = advance(pa);
+      }
+    if (TW > 1) {
+      qreg = load_q(pc);
+      wait_global_loads();
+    }
+
+    // Write out the state of the current item's segment, which ends at tile pc.j
+    // (tile x of all).
+    auto flush = [&](int x) __attribute__((always_inline)) {
+      const DecParams p = arguments();
+      const int item = pc.b * I + pc.r;
+      const int item_start = x - pc.j;  // flat index of the item's first tile
+      const bool ends = pc.j == pc.nt - 1;
+      bool valid;
+      const size_t qrow = query_row(p, pc, valid);
+      const float Lrow = halves_sum(lsum);
+      if (item_start >= x0 && ends) {
+        if (valid) {
+          const float inv = 1.f / Lrow;
+#pragma unroll
+          for (int db = 0; db < DB; ++db) {
+            bf16* op = p.O + qrow * D + 32 * db + 4 * g2;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              st_bf16x4(op + 8 * i, oacc[db][4 * i] * inv, oacc[db][4 * i + 1] * inv, oacc[db][4 * i + 2] * inv,
+                        oacc[db][4 * i + 3] * inv);
+          }
+          if (g2 == 0) p.LSE[qrow] = (m + __log2f(Lrow)) * LN2;
         }
-      if (g2 == 0) *reinterpret_cast<f32x4*>(pr + D) = f32x4{m, Lrow, 0.f, 0.f};
-    }
-    if (ends && lane == 0 && tw == 0) {
-      // the runs holding this item: from the one holding its first tile to this one
-      const int first = (int)((((long long)item_start + 1) * n - 1) / T);
-      p.desc[item] = DecRuns{first, gw};
-    }
-  };
+        if (lane == 0 && tw == 0) p.desc[item] = DecRuns{0, -1};
+        return;
+      }
+      if (valid) {
+        const int hkv = pc.r / ng;
+        float* pr = p.part + (dec_slot_row(p, gw, (size_t)pc.b * p.Hkv + hkv, pc.r - hkv * ng) + 32 * tw + l32) * PST;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const f32x4 v = {oacc[db][4 * i], oacc[db][4 * i + 1], oacc[db][4 * i + 2], oacc[db][4 * i + 3]};
+            *reinterpret_cast<f32x4*>(pr + 32 * db + 8 * i + 4 * g2) = v;
+          }
+        if (g2 == 0) *reinterpret_cast<f32x4*>(pr + D) = f32x4{m, Lrow, 0.f, 0.f};
+      }
+      if (ends && lane == 0 && tw == 0) {
+        // the runs holding this item: from the one holding its first tile to this one
+        const int first = (int)((((long long)item_start + 1) * n - 1) / T);
+        p.desc[item] = DecRuns{first, gw};
+      }
+    };
 
-  // One tile: `cur` holds the tile at pc; the copy of the tile NST - 1 ahead
-  // (at pa, if this run has one) goes to `nxt`, whose last readers are done.
-  // The restrict qualifiers tell the compiler that the copy in flight does not
-  // touch `cur`, so its reads need not wait for it.
-  auto step = [&](const char* __restrict__ cur, char* __restrict__ nxt, DecPos pn, bool copies,
-                  bool new_item, auto streamed) __attribute__((always_inline)) {
-    compute_fence();  // the reads of the buffer about to be refilled are done
-    if constexpr (TW == 1) {
-      // Query rows of the next item (the tile at pn) are loaded a tile ahead,
-      // after the wait for the current tile: copies and query loads complete in
-      // issue order.  (The query-row copy sits in both branches so that the
-      // compiler's own wait for it counts the copy just issued on the first one.)
-      if (copies) {
-        issue(pa, nxt, streamed);
-        wait_global_loads_but<(NST - 1) * 2 * NI>();  // the tile at pc has landed (this wave's own copy)
-        if (new_item) qreg = qnext;
-        if (pn.j == 0) qnext = load_q(pn);
+    // One tile: `cur` holds the tile at pc; the copy of the tile NST - 1 ahead
+    // (at pa, if this run has one) goes to `nxt`, whose last readers are done.
+    // The restrict qualifiers tell the compiler that the copy in flight does not
+    // touch `cur`, so its reads need not wait for it.
+    auto step = [&](const char* __restrict__ cur, char* __restrict__ nxt, DecPos pn, bool copies,
+                    bool new_item) __attribute__((always_inline)) {
+      compute_fence();  // the reads of the buffer about to be refilled are done
+      if constexpr (TW == 1) {
+        // Query rows of the next item (the tile at pn) are loaded a tile ahead,
+        // after the wait for the current tile: copies and query loads complete in
+        // issue order.  (The query-row copy sits in both branches so that the
+        // compiler's own wait for it counts the copy just issued on the first one.)
+        if (copies) {
+          issue(pa, nxt, streamed);
+          wait_global_loads_but<(NST - 1) * 2 * NI>();  // the tile at pc has landed (this wave's own copy)
+          if (new_item) qreg = qnext;
+          if (pn.j == 0) qnext = load_q(pn);
+        } else {
+          wait_global_loads();
+          if (new_item) qreg = qnext;
+        }
       } else {
-        wait_global_loads();
-        if (new_item) qreg = qnext;
+        if (copies) wait_global_loads_but<(NST - 2) * 2 * NI>();  // this wave's part of the tile at pc has landed
+        else wait_global_loads();
+        barrier_lds_only();  // ... every wave's; and all are done with `nxt`
+        if (copies) issue(pa, nxt, streamed);
+        // A new item's query rows, waited for at once: were they still in flight
+        // at the end of this branch, the compiler would wait for them, and so for
+        // every copy in flight, in front of each tile's first product (121 instead
+        // of 95 us for the call above).
+        if (new_item) {
+          qreg = load_q(pc);
+          wait_global_loads();
+        }
       }
-    } else {
-      if (copies) wait_global_loads_but<(NST - 2) * 2 * NI>();  // this wave's part of the tile at pc has landed
-      else wait_global_loads();
-      barrier_lds_only();  // ... every wave's; and all are done with `nxt`
-      if (copies) issue(pa, nxt, streamed);
-      // A new item's query rows, waited for at once: were they still in flight
-      // at the end of this branch, the compiler would wait for them, and so for
-      // every copy in flight, in front of each tile's first product (121 instead
-      // of 95 us for the call above).
-      if (new_item) {
-        qreg = load_q(pc);
-        wait_global_loads();
-      }
-    }
-    const int ntc = cdiv(pc.len, KT);
-    const int nvalid = pc.j < ntc ? pc.len - pc.j * KT : S - (pc.j - ntc) * KT;  // keys that exist
+      const int ntc = cdiv(pc.len, KT);
+      const int nvalid = pc.j < ntc ? pc.len - pc.j * KT : S - (pc.j - ntc) * KT;  // keys that exist
 
-    // S^T[key][query] = sum_d K[key][d] Q[query][d]
-    f32x16 sacc[KB];
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) sacc[kb][e] = 0.f;
-#pragma unroll
-    for (int s = 0; s < DS; ++s)
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) sacc[kb] = mfma32(lds_rows<D>(cur, ops.row_rel, s, kb), qreg.v[s], sacc[kb]);
-    pipeline_lds_reads<DS * KB, 4, 1>();  // operand reads four MFMAs ahead
-    if (nvalid < KT) {
+      // S^T[key][query] = sum_d K[key][d] Q[query][d]
+      f32x16 sacc[KB];
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4)
+        for (int e = 0; e < 16; ++e) sacc[kb][e] = 0.f;
 #pragma unroll
-          for (int jj = 0; jj < 4; ++jj)
-            if (32 * kb + 8 * i4 + 4 * g2 + jj >= nvalid) sacc[kb][4 * i4 + jj] = -INFINITY;
-    }
-    // (row maximum and row sum as balanced trees: no serial chains)
-    float m3[KB * 8];
+      for (int s = 0; s < DS; ++s)
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
+        for (int kb = 0; kb < KB; ++kb) sacc[kb] = mfma32(lds_rows<D>(cur, ops.row_rel, s, kb), qreg.v[s], sacc[kb]);
+      pipeline_lds_reads<DS * KB, 4, 1>();  // operand reads four MFMAs ahead
+      if (nvalid < KT) {
 #pragma unroll
-      for (int e = 0; e < 16; e += 2) m3[kb * 8 + e / 2] = fmaxf(sacc[kb][e], sacc[kb][e + 1]);
-    const float mx = halves_max(tree_max<KB * 8>(m3)) * p.c;
-    const bool grow = mx > m + DEC_SLACK;
-    if (__any(grow)) {
-      const float alpha = grow ? fast_exp2(m - mx) : 1.f;
-      m = grow ? mx : m;
-      lsum *= alpha;
+        for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
+          for (int i4 = 0; i4 < 4; ++i4)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
-    }
-    bf16x8 pb[2 * KB];
+            for (int jj = 0; jj < 4; ++jj)
+              if (32 * kb + 8 * i4 + 4 * g2 + jj >= nvalid) sacc[kb][4 * i4 + jj] = -INFINITY;
+      }
+      // (row maximum and row sum as balanced trees: no serial chains)
+      float m3[KB * 8];
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
+      for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) sacc[kb][e] = fast_exp2(sacc[kb][e] * p.c - m);
-      pb[2 * kb] = pack8(sacc[kb], 0);
-      pb[2 * kb + 1] = pack8(sacc[kb], 8);
-    }
-    lsum += tree_sum<KB>(sacc);
-    // O^T[d][query] += sum_key V^T[d][key] P^T[key][query]
+        for (int e = 0; e < 16; e += 2) m3[kb * 8 + e / 2] = fmaxf(sacc[kb][e], sacc[kb][e + 1]);
+      const float mx = halves_max(tree_max<KB * 8>(m3)) * p.c;
+      const bool grow = mx > m + DEC_SLACK;
+      if (__any(grow)) {
+        const float alpha = grow ? fast_exp2(m - mx) : 1.f;
+        m = grow ? mx : m;
+        lsum *= alpha;
 #pragma unroll
-    for (int c = 0; c < 2 * KB; ++c)
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
-        oacc[db] = mfma32(lds_tr<D>(cur + Smem::TILE, ops.tr_rel0, ops.tr_rel1, c, db), pb[c], oacc[db]);
-    pipeline_lds_reads<2 * KB * DB, 4, 2>();
-  };
+          for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
+      }
+      bf16x8 pb[2 * KB];
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sacc[kb][e] = fast_exp2(sacc[kb][e] * p.c - m);
+        pb[2 * kb] = pack8(sacc[kb], 0);
+        pb[2 * kb + 1] = pack8(sacc[kb], 8);
+      }
+      lsum += tree_sum<KB>(sacc);
+      // O^T[d][query] += sum_key V^T[d][key] P^T[key][query]
+#pragma unroll
+      for (int c = 0; c < 2 * KB; ++c)
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+          oacc[db] = mfma32(lds_tr<D>(cur + Smem::TILE, ops.tr_rel0, ops.tr_rel1, c, db), pb[c], oacc[db]);
+      // (one wave holds two items' query rows: with reads four MFMAs ahead it
+      // runs out of registers and the compiler drops the order altogether)
+      pipeline_lds_reads<2 * KB * DB, (TW == 1 ? 3 : 4), 2>();
+    };
 
-  uint32_t bcur = 0;                           // ring offset of the tile at pc
-  uint32_t bnxt = (NST - 1) * 2 * Smem::TILE;  // ring offset the copy NST - 1 ahead goes to
-  // (the loop twice: a branch around the copies inside a step costs the teams 4%)
-  auto all_steps = [&](auto streamed) __attribute__((always_inline)) {
+    uint32_t bcur = 0;                           // ring offset of the tile at pc
+    uint32_t bnxt = (NST - 1) * 2 * Smem::TILE;  // ring offset the copy NST - 1 ahead goes to
     for (int x = x0; x < x1; ++x) {
       const DecPos pn = advance(pc);
       const bool more = x + 1 < x1, copies = x + NST - 1 < x1;
-      step(ring + bcur, ring + bnxt, pn, copies, x > x0 && pc.j == 0, streamed);
+      step(ring + bcur, ring + bnxt, pn, copies, x > x0 && pc.j == 0);
       if (copies) pa = advance(pa);
       bnxt = bcur;
       bcur = bcur == (NST - 1) * 2 * Smem::TILE ? 0u : bcur + 2 * Smem::TILE;
       if (!more || pn.j == 0) {
-        flush();
-        if (more) {  // the next tile starts the next item
-          reset();
-          item_start += pc.nt;
-          seg_j0 = 0;
-        }
+        flush(x);
+        if (more) reset();  // the next tile starts the next item
       }
       pc = pn;
     }
   };
-  if (stream) all_steps(Flag<true>());
-  else all_steps(Flag<false>());
+  if (stream) run(Flag<true>());
+  else run(Flag<false>());
 }
 
 // Merge the runs of each query row of an item held by several teams:
