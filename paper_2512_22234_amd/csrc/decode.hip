@@ -101,8 +101,13 @@ __device__ inline int dec_runs(int runs, int T) { return imin(runs, cdiv(T, DEC_
 // MiB 189 and 186, 768 MiB 334 and 324; 512 rows, 375 MiB, the other way round:
 // 312 and 316).
 constexpr size_t DEC_STREAM_BYTES = (size_t)288 << 20;
-// First tile of run gw (the runs cut T tiles into n near-equal pieces).
-__device__ inline int dec_run_start(int gw, int n, int T) { return (int)(((long long)gw * T) / n); }
+// First tile of run gw <= n (the runs cut T tiles into n near-equal pieces).
+// RUNS, the teams of the grid, is a power of two, and T < n DEC_MIN_RUN + 1 where
+// fewer take part: no 64-bit division (three of them took 1 us of a call).
+template <int RUNS>
+__device__ inline int dec_run_start(int gw, int n, int T) {
+  return n == RUNS ? (int)(((long long)gw * T) / RUNS) : (int)((unsigned)(gw * T) / (unsigned)n);
+}
 // First row of the partial slot of run gw for row group g of (sequence, KV head) bh.
 __device__ inline size_t dec_slot_row(const DecParams& p, int gw, size_t bh, int g) {
   return (size_t)(gw + g) * p.grows + bh * p.hrows;
@@ -166,15 +171,20 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
     total += s;
   }
   const int excl = before + incl - csum;  // tiles per item of the sequences before c0
+  total = __builtin_amdgcn_readfirstlane(total);  // (so that all that follows from it is scalar)
   const int T = total * I;                // checked on the host to fit in 31 bits
-  const int n = dec_runs(p.runs, T);
-  const bool stream = (size_t)(total * p.Hkv) * (2 * Smem::TILE) > DEC_STREAM_BYTES;
-  // Consecutive runs go to different workgroups: where fewer teams than the
-  // grid holds take part, they are spread over the CUs.
+  constexpr int RUNS = DEC_WAVES / TW;    // teams of the grid
+  const int n = dec_runs(RUNS, T);
+  const bool stream = total * p.Hkv > (int)(DEC_STREAM_BYTES / (2 * Smem::TILE));
+  // Run of a workgroup's team v.  Consecutive runs share a workgroup (64
+  // sequences of up to 1024 tokens: 28.4 us, 28.8 spread over the workgroups;
+  // 32 sequences of 2200, S = 8: 56.0, 57.4), but where fewer teams than the
+  // grid holds take part they are spread over the CUs.
+  auto run_of = [&](int v) { return n == RUNS ? (int)blockIdx.x * TEAMS + v : v * (int)gridDim.x + (int)blockIdx.x; };
   // the thread whose sequences hold a team's first tile records where it lies
 #pragma unroll
   for (int v = 0; v < TEAMS; ++v) {
-    const int x0 = dec_run_start(v * gridDim.x + blockIdx.x, n, T);
+    const int x0 = dec_run_start<RUNS>(run_of(v), n, T);
     if (csum > 0 && excl * I <= x0 && x0 < (excl + csum) * I) {
       int pb = excl;
       for (int b = c0; b < c1; ++b) {
@@ -191,9 +201,9 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
   __syncthreads();
 
   // ---- this team's run ----
-  const int gw = tm * gridDim.x + blockIdx.x;
+  const int gw = run_of(tm);
   if (gw >= n) return;
-  const int x0 = dec_run_start(gw, n, T), x1 = dec_run_start(gw + 1, n, T);
+  const int x0 = dec_run_start<RUNS>(gw, n, T), x1 = dec_run_start<RUNS>(gw + 1, n, T);
   DecPos pc;
   pc.b = __builtin_amdgcn_readfirstlane(sm.start_b[tm]);
   const int off = __builtin_amdgcn_readfirstlane(sm.start_off[tm]);
