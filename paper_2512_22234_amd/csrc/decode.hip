@@ -294,19 +294,22 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
     };
     reset();
     char* const ring = sm.buf[tm];
-    if (TW == 1) qreg = load_q(pc);
+    // Query rows first: behind the copies, their latency came on top of the
+    // tiles' in front of the first product.
+    qreg = load_q(pc);
     // the first NST - 1 tiles (those this run has); pa: the next tile to copy
     DecPos pa = pc;
+    issue(pa, ring, streamed);
+    pa = advance(pa);
 #pragma unroll
-    for (int u = 0; u < NST - 1; ++u)
+    for (int u = 1; u < NST - 1; ++u)
       if (x0 + u < x1) {
         issue(pa, ring + u * 2 * Smem::TILE, streamed);
         pa = advance(pa);
       }
-    if (TW > 1) {
-      qreg = load_q(pc);
-      wait_global_loads();
-    }
+    // Teams: the query rows have landed once all but the newest tile have; one
+    // tile at least follows them on every path, so the compiler sees it too (step).
+    if (TW > 1) wait_global_loads_but<2 * NI>();
 
     // Write out the state of the current item's segment, which ends at tile pc.j
     // (tile x of all).
@@ -357,7 +360,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
     // (at pa, if this run has one) goes to `nxt`, whose last readers are done.
     // The restrict qualifiers tell the compiler that the copy in flight does not
     // touch `cur`, so its reads need not wait for it.
-    auto step = [&](const char* __restrict__ cur, char* __restrict__ nxt, DecPos pn, bool copies,
+    auto step = [&](const char* __restrict__ cur, char* __restrict__ nxt, DecPos pn, bool more, bool copies,
                     bool new_item) __attribute__((always_inline)) {
       compute_fence();  // the reads of the buffer about to be refilled are done
       if constexpr (TW == 1) {
@@ -375,18 +378,23 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
           if (new_item) qreg = qnext;
         }
       } else {
-        if (copies) wait_global_loads_but<(NST - 2) * 2 * NI>();  // this wave's part of the tile at pc has landed
-        else wait_global_loads();
-        barrier_lds_only();  // ... every wave's; and all are done with `nxt`
-        if (copies) issue(pa, nxt, streamed);
-        // A new item's query rows, waited for at once: were they still in flight
-        // at the end of this branch, the compiler would wait for them, and so for
-        // every copy in flight, in front of each tile's first product (121 instead
-        // of 95 us for the call above).
+        // The next item's query rows are loaded a tile ahead here as well, into
+        // registers that only the branch that takes them over reads, behind its
+        // own wait: were they still in flight at the end of it, the compiler would
+        // wait for them, and so for every copy in flight, in front of each tile's
+        // first product (121 instead of 95 us for the call above).
         if (new_item) {
-          qreg = load_q(pc);
+          wait_global_loads();
+          qreg = qnext;
+          compute_fence();  // (keeps this wait from being merged with those below)
+        } else if (copies) {
+          wait_global_loads_but<(NST - 2) * 2 * NI>();  // this wave's part of the tile at pc has landed
+        } else {
           wait_global_loads();
         }
+        barrier_lds_only();  // ... every wave's; and all are done with `nxt`
+        if (more && pn.j == 0) qnext = load_q(pn);
+        if (copies) issue(pa, nxt, streamed);
       }
       const int ntc = cdiv(pc.len, KT);
       const int nvalid = pc.j < ntc ? pc.len - pc.j * KT : S - (pc.j - ntc) * KT;  // keys that exist
@@ -453,7 +461,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
     for (int x = x0; x < x1; ++x) {
       const DecPos pn = advance(pc);
       const bool more = x + 1 < x1, copies = x + NST - 1 < x1;
-      step(ring + bcur, ring + bnxt, pn, copies, x > x0 && pc.j == 0);
+      step(ring + bcur, ring + bnxt, pn, more, copies, x > x0 && pc.j == 0);
       if (copies) pa = advance(pa);
       bnxt = bcur;
       bcur = bcur == (NST - 1) * 2 * Smem::TILE ? 0u : bcur + 2 * Smem::TILE;

@@ -154,10 +154,11 @@ def test_decode_full_workload_sampled_rows():
         _check(_np(o[b:b + 1, h:h + 1]), _np(lse[b:b + 1, h:h + 1]), Or, LSEr, f"full b{b} h{h} len{n}")
 
 
-@pytest.mark.parametrize("Hq,S", [(16, 32), (32, 32)])
+@pytest.mark.parametrize("Hq,S", [(16, 32), (32, 32), (32, 64)])
 def test_decode_streamed_teams_sampled_rows(Hq, S):
     """More keys and values than the last-level cache holds (340 MB), so the
-    teams of two and of four waves load them nontemporal; sampled heads."""
+    teams of two and of four waves (the last one in two row groups) load them
+    nontemporal; sampled heads."""
     B, Hkv, D, C = 40, 8, 128, 2080
     lens = [C - 3 * b for b in range(B)]
     q, kc, vc, kn, vn, cl = make_decode_inputs(B, Hq, Hkv, D, S, C, lens, seed=45, device="cuda")
