@@ -262,10 +262,12 @@ size_t bd_attn_varlen_workspace_bytes(int n_seqs, int total_L, int max_L, int S,
  *   kernels only (the host never waits for it).  Values are clamped to
  *   [0, capacity].  capacity <= 2^22; capacity = 0 allows NULL caches.
  * dtype: BD_ATTN_BF16 only (anything else is BD_ATTN_ERR_UNSUPPORTED).
- * The key tiles of all sequences and heads are shared out evenly over a
- * fixed set of waves, whatever the lengths; a KV head's keys split over
- * several waves are merged by a second kernel (the result depends on the
- * lengths of the other sequences only through float32 rounding).
+ * The key tiles of all sequences and heads are shared out evenly over teams
+ * of one, two or four waves (by the query rows per KV head), as many teams as
+ * the device holds but at least two tiles for each, whatever the lengths; a KV
+ * head's keys split over several teams are merged by a second kernel (the
+ * result depends on the lengths of the other sequences only through where
+ * their tiles cut its keys: the rounding of P to bfloat16 and of float32 sums).
  * ws/ws_bytes: device workspace of at least bd_attn_decode_workspace_bytes
  *   bytes (16-byte aligned; it need not be initialised).
  * Ownership, stream order and errors are as for bd_attn_fwd.
@@ -311,7 +313,9 @@ int bd_lce_fwd(const void* H, const void* W, const int32_t* targets, int N, int 
  *   dH = g W  ([N, Dm] bf16),   dW = g^T H  ([V, Dm] bf16).
  * g is formed from the logits kept by bd_lce_fwd when `logits` is not NULL,
  * else recomputed from H and W (one more GEMM), and held in the workspace as
- * bf16 ([N, V rounded up to 256]).
+ * bf16 ([N, V rounded up to 256]).  dH is summed over one or more parts of the
+ * vocabulary, whose float32 sums lie in dW until dW itself is written: dW holds
+ * nothing of use before the call's work has completed.
  */
 int bd_lce_bwd(const void* H, const void* W, const int32_t* targets, const float* LSE, const float* dlogp,
                const float* logits, int N, int V, int Dm, int dtype, void* dH, void* dW, void* ws, size_t ws_bytes,
