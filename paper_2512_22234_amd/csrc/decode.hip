@@ -34,9 +34,9 @@
 //   TW = 2, 4 (up to 64 rows, more): a workgroup is one team, whose waves share
 //     each tile, so a KV row is fetched once for up to 128 query rows; one
 //     barrier per tile.  24 sequences of 512..8192 tokens, 32 query and 8 KV
-//     heads of 128, S = 32 (128 rows per KV head, 370 MB): 93 us; with one wave
-//     per 32 rows, which fetched the cache four times, 203 us.  (Tiles of 32
-//     keys: 104 us; eight waves, half the keys of a tile each: 95 us.)
+//     heads of 128, S = 32 (128 rows per KV head, 370 MB): 91 us; with one wave
+//     per 32 rows, which fetched the cache four times, 203 us.  (At 93 us, with
+//     tiles of 32 keys 104; with eight waves, half the keys of a tile each, 95.)
 // Per tile: S^T = K Q^T (a lane owns a query column, as in the forward pass),
 // P = exp2(c S - m) against a lazily moved reference max, O^T += V^T P^T with
 // V^T read through the transposing LDS read.

@@ -20,9 +20,10 @@
 // step so that the operand reads of the next chunk overlap that step's MFMAs.
 // Chunks of 64 make the rows of a ROW tile whole 128-byte cache lines: chunks
 // of 32 fetched every line of L2 twice (4096 x 151,936 x 4096: forward 4.54 ->
-// 3.83 ms, recompute 4.78 -> 4.01, dH 4.15 -> 3.66, dW 4.66 -> 4.11, 1240 to
-// 1390 TFLOP/s; a fourth 32-wide stage of lookahead alone changed nothing, and
-// 256 x 128 tiles at two workgroups per CU took 5.2 ms).  An operand tile is
+// 3.83 ms, recompute 4.78 -> 4.01, dH 4.15 -> 3.66, dW 4.66 -> 4.11, that is
+// 1330, 1270, 1390 and 1240 TFLOP/s now; a fourth 32-wide stage of lookahead
+// alone changed nothing, and 256 x 128 tiles at two workgroups per CU took 5.2
+// ms).  An operand tile is
 // either ROW (256 rows of 64 k values: the k index is contiguous in memory)
 // or TR (64 k rows of 256 values: the other index is contiguous), read with
 // row-slice or transposing LDS reads in the same k order.  Output rows are
