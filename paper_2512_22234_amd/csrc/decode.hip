@@ -83,11 +83,18 @@ __device__ inline int dec_tiles(const DecParams& p, int len) {
   return cdiv(len, KT) + cdiv(p.S, KT);
 }
 // Teams that take part in a call of T tiles on a grid of `runs` teams: at
-// least about DEC_MIN_RUN tiles each, so that a short call is not cut into
-// single tiles with as many partial results to merge (1, 2 and 4 measured the
-// same within 2% on one sequence of 1500 tokens), and no run is empty (T >= 1).
-constexpr int DEC_MIN_RUN = 2;
-__device__ inline int dec_runs(int runs, int T) { return imin(runs, cdiv(T, DEC_MIN_RUN)); }
+// least about DEC_MIN_RUN tiles for each team of several waves, so that a short
+// call is not cut into single tiles with as many partial results of its many
+// rows to merge (30 sequences of 30 to 60 tokens, S = 32: 15.7 us, single tiles
+// 23.0), and no run is empty (T >= 1).  One wave takes single tiles: the same
+// time within 2% on one sequence of 1500 tokens, and the nearest to float64,
+// since the largest P of a run is 1 exactly (relative error 2.28e-3, with two
+// tiles a run 2.32e-3).
+template <int TW>
+__device__ inline int dec_runs(int runs, int T) {
+  constexpr int DEC_MIN_RUN = TW == 1 ? 1 : 2;
+  return imin(runs, cdiv(T, DEC_MIN_RUN));
+}
 // Keys and values of more than 288 MiB, beyond the 256 MiB of the last-level
 // cache, are loaded nontemporal: nothing of them survives to the next call, and
 // without their lines in L2 and the last-level cache the same bytes come faster
@@ -102,8 +109,8 @@ __device__ inline int dec_runs(int runs, int T) { return imin(runs, cdiv(T, DEC_
 // 312 and 316).
 constexpr size_t DEC_STREAM_BYTES = (size_t)288 << 20;
 // First tile of run gw <= n (the runs cut T tiles into n near-equal pieces).
-// RUNS, the teams of the grid, is a power of two, and T < n DEC_MIN_RUN + 1 where
-// fewer take part: no 64-bit division (three of them took 1 us of a call).
+// RUNS, the teams of the grid, is a power of two, and T <= 2 n where fewer take
+// part: no 64-bit division (three of them took 1 us of a call).
 template <int RUNS>
 __device__ inline int dec_run_start(int gw, int n, int T) {
   return n == RUNS ? (int)(((long long)gw * T) / RUNS) : (int)((unsigned)(gw * T) / (unsigned)n);
@@ -174,7 +181,7 @@ __global__ __launch_bounds__(TW == 1 ? 256 : 64 * TW, 1) void dec_kernel(DecPara
   total = __builtin_amdgcn_readfirstlane(total);  // (so that all that follows from it is scalar)
   const int T = total * I;                // checked on the host to fit in 31 bits
   constexpr int RUNS = DEC_WAVES / TW;    // teams of the grid
-  const int n = dec_runs(RUNS, T);
+  const int n = dec_runs<TW>(RUNS, T);
   const bool stream = total * p.Hkv > (int)(DEC_STREAM_BYTES / (2 * Smem::TILE));
   // Run of a workgroup's team v.  Consecutive runs share a workgroup (64
   // sequences of up to 1024 tokens: 28.4 us, 28.8 spread over the workgroups;
